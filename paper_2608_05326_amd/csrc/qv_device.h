@@ -69,6 +69,8 @@ struct MigrateArgs {
   const uint16_t* src_v;
   int32_t src_T;
   const int32_t* gate_fail; // as RetierArgs::gate_fail
+  int32_t n_quant_blocks;   // workgroups (of a grid row) that take quantizations; the others take promotions
+  int32_t n_promote_blocks;
 };
 
 struct KeyNormArgs {        // key-norm scores of the prompt windows
@@ -123,14 +125,15 @@ struct ScorePowArgs {       // p-norm ranking: prompt scores raised to the power
   float p;
 };
 
-struct PackArgs {           // copy prompt tokens into ring / sink slots
+struct PackArgs {           // copy the prompt's sink tokens and tail into sink / ring slots
   Geometry g;
   UnitLayout L;
   uint8_t* base;
   const uint16_t* src_k;
   const uint16_t* src_v;
   int32_t src_T;
-  int32_t tok0, tok1;       // token range [tok0, tok1) to copy
+  int32_t n_sink;           // tokens [0, n_sink) and [tail0, src_T) are copied
+  int32_t tail0;
 };
 
 __device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }

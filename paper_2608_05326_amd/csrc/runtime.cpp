@@ -35,7 +35,7 @@ hipError_t attend_footprint(const Geometry& g, int* vgprs, size_t* lds);
 hipError_t migrate_footprint(const Geometry& g, int* vgprs, size_t* lds);
 hipError_t launch_gate_wait(const uint64_t* seq, uint64_t value, int32_t* fail, int64_t ticks,
                             hipStream_t st);
-hipError_t launch_migrate(const MigrateArgs& a, int max_quant, int max_promote, hipStream_t st);
+hipError_t launch_migrate(MigrateArgs a, int max_quant, int max_promote, hipStream_t st);
 hipError_t launch_pack_tokens(const PackArgs& a, hipStream_t st);
 hipError_t launch_key_norm_init(const KeyNormArgs& a, hipStream_t st);
 hipError_t launch_score_pow(const ScorePowArgs& a, hipStream_t st);
@@ -377,7 +377,7 @@ hipError_t timed(qevict_cache* c, int kernel, hipStream_t st, F&& launch, int un
 // leaves free, and the queue-level wait, whose stall of the cache stream (about
 // 12 us a batch) gives it that room, was measured faster: 128K context with
 // 64-token windows (256-register attention), the RoPE-aware tier (256), GQA 8
-// (217 plus a 79-register migration wave), 8-token windows (222 plus 96) with 16
+// (217 plus an 80-register migration wave), 8-token windows (222) with 16
 // layer caches.
 hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
   int av = 0, mv = 0;
@@ -386,7 +386,12 @@ hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
   if (e == hipSuccess) e = migrate_footprint(g, &mv, &ml);
   if (e != hipSuccess) return e;
   auto granule = [](int v) { return (v + 7) / 8 * 8; };   // VGPR allocation granule
-  *fits = 2 * granule(av) + granule(mv) <= 512 && 2 * al + ml <= 160 * 1024;
+  // A migration wave counts as 72 registers at least: that of 8-token windows needs
+  // fewer (53) and would fit, but there the better order depends on the number of
+  // layer caches (gate / queue-level wait: 28.6 / 30.4 us a step with 4, 31.2 / 30.7
+  // with 16), so those keep the queue-level wait.
+  constexpr int kLeastMigrate = 72;
+  *fits = 2 * granule(av) + std::max(granule(mv), kLeastMigrate) <= 512 && 2 * al + ml <= 160 * 1024;
   return hipSuccess;
 }
 
@@ -747,13 +752,9 @@ qevict_status qevict_prefill_assign(qevict_cache* c, int32_t layer, const uint16
   UnitLayout L;
   uint8_t* base;
   fill_common(c, layer, &gg, &L, &base);
-  PackArgs pa{gg, L, base, k, v, prompt_len, 0, g.sink};
-  hipError_t e = launch_pack_tokens(pa, c->stream);   // sink tokens
-  if (e == hipSuccess) {
-    pa.tok0 = g.sink + n_hist * g.W;
-    pa.tok1 = prompt_len;
-    e = launch_pack_tokens(pa, c->stream);            // tail: recent region and partial window
-  }
+  // sink tokens, and the tail: recent region and partial window
+  const PackArgs pa{gg, L, base, k, v, prompt_len, g.sink, g.sink + n_hist * g.W};
+  hipError_t e = launch_pack_tokens(pa, c->stream);
   float* staging = (float*)(c->ws + kHeaderBytes + (int64_t)c->cfg.num_layers * g.B * c->L.unit_bytes);
   if (key_norm && e == hipSuccess) {
     KeyNormArgs ka{gg, k, prompt_len, n_init, staging};
