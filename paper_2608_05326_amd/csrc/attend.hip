@@ -1429,10 +1429,17 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
 // window's cumulative score.  Every thread issues all of its global loads in
 // one round; the reductions run in a fixed order, so results do not depend
 // on timing.
+// Bound by its launch and the latency of that round.  The loads are unconditional
+// at clamped rows (a guarded load is a branch with its own address arithmetic: 32
+// guarded statistics loads a thread, of which four or eight were used, were 600
+// instructions, and at 1200 mass blocks bound the kernel): 4.5 -> 4.0 us at 32 heads
+// x 64 splits (8B, 32K), 8.8 -> 7.5 us at 4 x 64 heads x 16 splits (70B, 64K),
+// 4.3 -> 3.4 us at 8 heads (2K).
 constexpr int kMergeThreads = 256;
 constexpr int kSplitGroups = 8;                     // split rows handled in parallel per output block
 
-// NSPT: split rows one output-block thread reads (>= S / 8)
+// NSPT: split rows one output-block thread reads in its first round (further
+// splits, only with an explicit split count above 64, are read one by one)
 // Score update of the merge: attention masses (cumulative or decayed), the
 // attention p-norm, or key norms (separate instantiations, so the default one
 // carries no code of the others)
@@ -1458,19 +1465,25 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
     // ---- output of head h: thread (c4, grp) owns channels 4c4..4c4+3 of splits grp + 8i ----
     const int h = blk;
     const int c4 = tid & 31, grp = tid >> 5;
+    // rounds of NSPT rows a thread (one round with at most 8 NSPT splits); rows past
+    // the last split are read again and not used
+    auto stat = [&](int sp) {
+      float2 v = pml[(int64_t)h * S + min(sp, S - 1)];
+      v.x = sp < S ? v.x : -INFINITY;
+      return v;
+    };
     float4 o[NSPT];
     float2 ml[NSPT];
 #pragma unroll
     for (int i = 0; i < NSPT; ++i) {
       const int sp = grp + kSplitGroups * i;
-      const bool ok = sp < S;
-      o[i] = ok ? *(const float4*)(part + ((int64_t)h * S + sp) * kHeadDim + 4 * c4)
-                : make_float4(0.f, 0.f, 0.f, 0.f);
-      ml[i] = ok ? pml[(int64_t)h * S + sp] : make_float2(-INFINITY, 0.f);
+      o[i] = *(const float4*)(part + ((int64_t)h * S + min(sp, S - 1)) * kHeadDim + 4 * c4);
+      ml[i] = stat(sp);
     }
     float m = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NSPT; ++i) m = fmaxf(m, ml[i].x);
+    for (int sp = grp + kSplitGroups * NSPT; sp < S; sp += kSplitGroups) m = fmaxf(m, stat(sp).x);
     if (c4 == 0) sml[0][grp] = m;
     __syncthreads();
     float M = -INFINITY;
@@ -1478,16 +1491,19 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
     for (int q = 0; q < kSplitGroups; ++q) M = fmaxf(M, sml[0][q]);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float lsum = 0.f;
+    auto add = [&](float4 x, float2 st) {
+      const float f = __builtin_amdgcn_exp2f(st.x - M);   // 0 for a split without items
+      acc.x += f * x.x;
+      acc.y += f * x.y;
+      acc.z += f * x.z;
+      acc.w += f * x.w;
+      lsum += f * st.y;
+    };
     if (M > -INFINITY) {
 #pragma unroll
-      for (int i = 0; i < NSPT; ++i) {
-        const float f = ml[i].x > -INFINITY ? __builtin_amdgcn_exp2f(ml[i].x - M) : 0.f;
-        acc.x += f * o[i].x;
-        acc.y += f * o[i].y;
-        acc.z += f * o[i].z;
-        acc.w += f * o[i].w;
-        lsum += f * ml[i].y;
-      }
+      for (int i = 0; i < NSPT; ++i) add(o[i], ml[i]);
+      for (int sp = grp + kSplitGroups * NSPT; sp < S; sp += kSplitGroups)
+        add(*(const float4*)(part + ((int64_t)h * S + sp) * kHeadDim + 4 * c4), stat(sp));
     }
     sred[grp][c4] = acc;
     if (c4 == 0) sml[1][grp] = lsum;
@@ -1527,36 +1543,41 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
   const float2* __restrict__ mref = (const float2*)(ub + a.L.mref);
   const int32_t* __restrict__ iwin = (const int32_t*)(ub + a.L.item_win);
   float* iscore = (float*)(ub + a.L.item_score);
-  const bool maybe = in_blk && pos < G.max_items;
-  const float2 mr = maybe ? mref[(int64_t)pos * nh + hh] : make_float2(-INFINITY, 0.f);
-  const int wl = (maybe && hh == 0) ? iwin[min(pos, G.max_fq)] : -1;   // used when pos < n_fq
-  const float old_score = (maybe && hh == 0) ? iscore[pos] : 0.f;
+  // (unconditional loads at clamped positions: guarded ones cost a branch each)
+  const int cpos = min(pos, G.max_items - 1);
+  const float2 mr = mref[(int64_t)cpos * nh + hh];
+  const int wl = iwin[min(pos, G.max_fq)];   // used when pos < n_fq
+  const float old_score = iscore[cpos];
   // M_h, L_h: P consecutive threads per head (P a power of two, P * H_q <= 256,
   // P <= 64 so that the P threads of a head sit in one wave), thread j folds
   // splits j, j + P, j + 2P, ... (consecutive threads read consecutive rows),
   // then a butterfly over the P lanes combines the (max, sum) pairs
   int P = 1;
   while (2 * P * nh <= kMergeThreads && P < 64) P *= 2;
-  const int C = (S + P - 1) / P;
-  // C <= 32: with P = 64, S <= 256 splits; otherwise P * H_q > 128 and S * H_q <= 4096
-  constexpr int kMaxC = 32;
+  // splits in rounds of kRound rows a thread (one round with the automatic split
+  // counts); each round's loads are issued together
+  constexpr int kRound = 8;
   {
-    const int h = tid / P, j = tid % P;
-    const bool hv = h < nh;
-    float2 st[kMaxC];
+    const int h = min(tid / P, nh - 1), j = tid % P;
+    const bool hv = tid / P < nh;
+    const float2* row = pml + (int64_t)h * S;
+    float m = -INFINITY, l = 0.f;
+    for (int sp0 = j; sp0 - j < S; sp0 += kRound * P) {
+      float2 st[kRound];
 #pragma unroll
-    for (int i = 0; i < kMaxC; ++i) {
-      const int sp = j + P * i;
-      st[i] = (hv && i < C && sp < S) ? pml[(int64_t)h * S + sp] : make_float2(-INFINITY, 0.f);
-    }
-    float m = -INFINITY;
+      for (int i = 0; i < kRound; ++i) st[i] = row[min(sp0 + P * i, S - 1)];
+      float mn = m;
 #pragma unroll
-    for (int i = 0; i < kMaxC; ++i) m = fmaxf(m, st[i].x);
-    float l = 0.f;
-    if (m > -INFINITY) {
+      for (int i = 0; i < kRound; ++i) {
+        st[i].x = sp0 + P * i < S ? st[i].x : -INFINITY;
+        mn = fmaxf(mn, st[i].x);
+      }
+      if (mn > -INFINITY) {
+        l = m > -INFINITY ? l * __builtin_amdgcn_exp2f(m - mn) : 0.f;
 #pragma unroll
-      for (int i = 0; i < kMaxC; ++i)
-        if (st[i].x > -INFINITY) l += st[i].y * __builtin_amdgcn_exp2f(st[i].x - m);
+        for (int i = 0; i < kRound; ++i) l += st[i].y * __builtin_amdgcn_exp2f(st[i].x - mn);   // exp2(-inf) = 0
+        m = mn;
+      }
     }
     for (int o = 1; o < P; o <<= 1) {
       const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64);
@@ -1711,8 +1732,7 @@ hipError_t launch_merge(const AttnArgs& a, hipStream_t st) {
   auto by_split = [&](auto ms) {
     constexpr int MS = decltype(ms)::value;
     if (need <= 4) go(k_merge<4, MS>);
-    else if (need <= 8) go(k_merge<8, MS>);
-    else go(k_merge<32, MS>);
+    else go(k_merge<8, MS>);
   };
   if (a.key_norm) by_split(std::integral_constant<int, kScoreKeyNorm>{});
   else if (a.pnorm_p > 0.f) by_split(std::integral_constant<int, kScorePNorm>{});
