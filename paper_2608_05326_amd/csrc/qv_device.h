@@ -103,6 +103,25 @@ __device__ __forceinline__ float rows_sum(float x) {
   return __uint_as_float(b0) + __uint_as_float(b1);
 }
 
+// Reads one word of every 64-byte line of the kernel's argument block (a struct of
+// BYTES bytes) and waits for them once; returns 0, to be added to a value the kernel
+// needs first.  The compiler loads arguments where it first needs them, so a kernel
+// whose arguments span eight lines meets a miss of the scalar cache (several hundred
+// ns: the block lies in device memory) in each of the few dependent steps of its
+// prologue; after this they hit.  (Not a volatile asm: after one the compiler no
+// longer reads uniform memory with scalar loads.)
+template <int BYTES>
+__device__ __forceinline__ int touch_kernargs() {
+  typedef __attribute__((address_space(4))) const uint32_t word;
+  word* p = (word*)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t x = 0;
+#pragma unroll
+  for (int i = 0; i < (BYTES + 63) / 64; ++i) x |= p[16 * i];
+  int zero;
+  asm("s_mov_b32 %0, 0" : "=s"(zero) : "s"(x));
+  return zero;
+}
+
 struct ObsArgs {            // initial window scores from the observation queries' attention
   const uint16_t* q;        // [B][H_q][n_obs][d] bf16
   const uint16_t* k;        // [B][H_kv][T][d] bf16
@@ -110,9 +129,9 @@ struct ObsArgs {            // initial window scores from the observation querie
   int32_t cbase;            // first key of chunk 0 (sink - 64 n_pre, <= 0)
   int32_t n_pre;            // chunks before the first window (sink keys)
   int32_t n_chunks;         // chunks of 64 keys
-  int32_t n_blk;            // workgroups of four chunks
   float scale_log2;
-  float2* cml;              // [B][H_kv][n_chunks][n_rows] (max, exp-sum) per chunk and row
+  float* cm;                // [B][H_kv][n_chunks][n_rows] logit max (log2 units) per chunk and row
+  float* cl;                // the same layout: exp-sum relative to it
   float* wl;                // [B][H_kv][n_w][n_rows] window exp-sum relative to its chunk's max
   float2* row_ml;           // [B][H_kv][n_rows] (M, 1 / L)
   float* scores;            // [B][n_w]

@@ -868,10 +868,10 @@ static qevict_status prefill_scores_impl(qevict_cache* c, const uint16_t* q_obs,
   a.n_pre = sh.n_pre;
   a.cbase = g.sink - kObsChunk * sh.n_pre;
   a.n_chunks = sh.n_chunks;
-  a.n_blk = ceil_div(sh.n_chunks, 4);
   a.scale_log2 = g.scale_log2;
   uint8_t* sb = (uint8_t*)scratch;
-  a.cml = (float2*)(sb + L.cml);
+  a.cm = (float*)(sb + L.cml);   // the maxima, then the exp-sums
+  a.cl = a.cm + (int64_t)g.B * g.H_kv * sh.n_chunks * a.n_rows;
   a.wl = (float*)(sb + L.wl);
   a.row_ml = (float2*)(sb + L.row_ml);
   a.scores = scores;
