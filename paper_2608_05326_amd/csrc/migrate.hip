@@ -758,7 +758,7 @@ constexpr int migrate_waves_per_simd() { return W == 64 ? (ROPE ? 3 : 4) : (ROPE
 template <int W, bool ROPE>
 __global__ __launch_bounds__(kMigrateThreads, (migrate_waves_per_simd<W, ROPE>())) void k_migrate(MigrateArgs a) {
   const Geometry& G = a.g;
-  const int b = blockIdx.y;
+  const int b = blockIdx.y + touch_kernargs<sizeof(MigrateArgs)>();
   __shared__ __attribute__((aligned(16))) MigrateLds<W> sm;
   // Everything up to the first task in two rounds of loads without a branch between
   // them: the arguments; then the count, the first entry and the gate word.  (A

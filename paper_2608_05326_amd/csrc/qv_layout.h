@@ -57,6 +57,7 @@ namespace qv {
 constexpr int kHeadDim = 128;
 constexpr int kMaxGqa = 16;
 constexpr int kMaxCand = 4096;      // candidates per routing event (one workgroup sorts them)
+constexpr int kMaxSplits = 256;     // split-K factor of the attention pass
 constexpr int kAttnThreads = 256;
 constexpr int kRetierThreads = 1024;
 

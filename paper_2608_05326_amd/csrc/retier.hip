@@ -1,7 +1,7 @@
 // Routing event: re-rank the candidate windows and re-tier them
 // (QEvict Sec. 4.3 candidate pool and TopK equations; Algorithm 1).
 //
-// One 1024-thread workgroup per sequence:
+// One workgroup per sequence (256, 512 or 1024 threads by the cache's size):
 //   1. candidates = current Full and Quantized windows (the live list, in
 //      window order) followed by the windows that left the recent region;
 //   2. 64-bit keys (score descending, then window ascending) define the total
@@ -17,6 +17,8 @@
 //      prefix sums (deterministic), and the quantize / promote work lists and
 //      the new live list (window order, with split-balancing cost prefix) are
 //      written for the kernels that follow on the stream.
+#include <algorithm>
+
 #include "qv_device.h"
 
 namespace qv {
@@ -86,17 +88,16 @@ __device__ __forceinline__ void block_scan_multi(int32_t* const (&buf)[NV], cons
 }
 
 // Exclusive prefix counts of NV flag arrays held in registers in strided
-// layout (element c = tid + k * kRetierThreads, k < PER): rank[v][k] = set flags
+// layout (element c = tid + k * NT, k < PER): rank[v][k] = set flags
 // before element c, tot[v] = set flags in all.  Only slices k < kmax (uniform)
 // may hold set flags; the others are skipped.  Wave ballots, then one wave per
 // array scans the (slice, wave) counts; two barriers.
-template <int NV>
-__device__ __forceinline__ void flag_scan(const bool (&f)[NV][kMaxCand / kRetierThreads],
-                                          int (&rank)[NV][kMaxCand / kRetierThreads], int (&tot)[NV],
+template <int NT, int PER, int NV>
+__device__ __forceinline__ void flag_scan(const bool (&f)[NV][PER],
+                                          int (&rank)[NV][PER], int (&tot)[NV],
                                           int32_t* tmp /* >= NV * 64 + NV */, int kmax) {
-  constexpr int PER = kMaxCand / kRetierThreads;
-  constexpr int NW = kRetierThreads / 64;
-  static_assert(PER * NW == 64, "one wave scans the slice counts");
+  constexpr int NW = NT / 64;
+  static_assert(PER * NW <= 64, "one wave scans the slice counts");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
@@ -110,11 +111,11 @@ __device__ __forceinline__ void flag_scan(const bool (&f)[NV][kMaxCand / kRetier
     }
   }
   __syncthreads();
-  if (wave < NV) {
-    const int x = lane < kmax * NW ? tmp[wave * 64 + lane] : 0;
+  for (int v = wave; v < NV; v += NW) {
+    const int x = lane < kmax * NW ? tmp[v * 64 + lane] : 0;
     const int inc = wave_inclusive_scan(x);
-    tmp[wave * 64 + lane] = inc - x;
-    if (lane == 63) tmp[NV * 64 + wave] = inc;
+    tmp[v * 64 + lane] = inc - x;
+    if (lane == 63) tmp[NV * 64 + v] = inc;
   }
   __syncthreads();
 #pragma unroll
@@ -347,17 +348,17 @@ struct SelLds {
   int32_t br[3], bcnt[3];
 };
 
-__device__ void select_thresholds(const uint64_t (&key)[kMaxCand / kRetierThreads], int kc, int n_cand,
+template <int NT, int PER>
+__device__ void select_thresholds(const uint64_t (&key)[PER], int kc, int n_cand,
                                   const int (&target)[3], int want, SelLds& s, uint64_t (&thr)[3]) {
-  constexpr int PER = kMaxCand / kRetierThreads;
-  constexpr int NW = kRetierThreads / 64;
+  constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int i = tid; i < 3 * kSelBuckets; i += kRetierThreads) (&s.hist[0][0])[i] = 0;
+  for (int i = tid; i < 3 * kSelBuckets; i += NT) (&s.hist[0][0])[i] = 0;
   if (tid < 3) s.nlist[tid] = 0;
   uint64_t mn = ~0ull, mx = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    if (k < kc && tid + k * kRetierThreads < n_cand) {
+    if (k < kc && tid + k * NT < n_cand) {
       mn = key[k] < mn ? key[k] : mn;
       mx = key[k] > mx ? key[k] : mx;
     }
@@ -407,7 +408,7 @@ __device__ void select_thresholds(const uint64_t (&key)[kMaxCand / kRetierThread
     if (!any) break;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      if (k >= kc || tid + k * kRetierThreads >= n_cand) continue;
+      if (k >= kc || tid + k * NT >= n_cand) continue;
       const uint64_t x = key[k];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
@@ -465,7 +466,7 @@ __device__ void select_thresholds(const uint64_t (&key)[kMaxCand / kRetierThread
   // the keys left in each interval, ranked pairwise
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    if (k >= kc || tid + k * kRetierThreads >= n_cand) continue;
+    if (k >= kc || tid + k * NT >= n_cand) continue;
     const uint64_t x = key[k];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -518,11 +519,11 @@ __device__ __forceinline__ void wave_minmax_u32(uint32_t& mn, uint32_t& mx) {
 // heavy clustering) falls back to the general refinement (select_thresholds).
 // Result: bit i of below[k] is set when key k lies below position target[i]
 // (always set for a target past the last candidate or not asked for).
-__device__ void select_tiers(const uint64_t (&key)[kMaxCand / kRetierThreads], int kc, int n_cand,
+template <int NT, int PER>
+__device__ void select_tiers(const uint64_t (&key)[PER], int kc, int n_cand,
                              const int (&target)[3], int want, SelLds& s,
-                             uint32_t (&below)[kMaxCand / kRetierThreads]) {
-  constexpr int PER = kMaxCand / kRetierThreads;
-  constexpr int NW = kRetierThreads / 64;
+                             uint32_t (&below)[PER]) {
+  constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   bool act[3];
   bool any = false;
@@ -549,7 +550,7 @@ __device__ void select_tiers(const uint64_t (&key)[kMaxCand / kRetierThreads], i
   const int sh = bl > 10 ? bl - 10 : 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    if (k >= kc || tid + k * kRetierThreads >= n_cand) continue;
+    if (k >= kc || tid + k * NT >= n_cand) continue;
     atomicAdd(&s.hist[0][((uint32_t)(key[k] >> 32) - mn) >> sh], 1);
   }
   __syncthreads();
@@ -604,7 +605,7 @@ __device__ void select_tiers(const uint64_t (&key)[kMaxCand / kRetierThreads], i
   }
   if (big) {
     uint64_t thr[3];
-    select_thresholds(key, kc, n_cand, target, want, s, thr);
+    select_thresholds<NT, PER>(key, kc, n_cand, target, want, s, thr);
 #pragma unroll
     for (int k = 0; k < PER; ++k)
       below[k] = (key[k] < thr[0] ? 1u : 0u) | (key[k] < thr[1] ? 2u : 0u) | (key[k] < thr[2] ? 4u : 0u);
@@ -613,7 +614,7 @@ __device__ void select_tiers(const uint64_t (&key)[kMaxCand / kRetierThreads], i
   if (need_list) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      if (k >= kc || tid + k * kRetierThreads >= n_cand) continue;
+      if (k >= kc || tid + k * NT >= n_cand) continue;
       const uint64_t x = key[k];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
@@ -626,7 +627,7 @@ __device__ void select_tiers(const uint64_t (&key)[kMaxCand / kRetierThreads], i
   }
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    if (k >= kc || tid + k * kRetierThreads >= n_cand) continue;
+    if (k >= kc || tid + k * NT >= n_cand) continue;
     const uint64_t x = key[k];
     uint32_t m = 0;
 #pragma unroll
@@ -649,17 +650,26 @@ __device__ void select_tiers(const uint64_t (&key)[kMaxCand / kRetierThreads], i
   }
 }
 
-__global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
+// NT threads of PER candidates (and slots) each; ONE_WAY: with the one-way policy's
+// sort.  Bound by issue and latency: a chain of a dozen barrier-separated steps on a
+// single workgroup.  The 4096-candidate form holds four slices of everything in every
+// thread (57 KB of code, 97 KB of LDS, 16 waves), so smaller caches take a form that
+// fits them: 10.3 -> 6.7 us at 40 candidates (256 threads); at 512, beside attention,
+// 14.6 -> 10.4 us with 1024 threads and 9.1 us with 512; 12.8 -> 10.0 us at 821 (1024).
+template <int NT, int PER, bool ONE_WAY>
+__global__ __launch_bounds__(NT) void k_retier(RetierArgs a) {
   const Geometry& G = a.g;
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = blockIdx.x + touch_kernargs<sizeof(RetierArgs)>(), tid = threadIdx.x;
   const RetierUnit& U = a.unit[blockIdx.y];   // this workgroup's layer
-  constexpr int NT = kRetierThreads;
-  constexpr int PER = kMaxCand / NT;
+  constexpr int CAP = NT * PER;
+  static_assert(!ONE_WAY || CAP == kMaxCand, "the sorts take the full capacity");
 
-  __shared__ __attribute__((aligned(16))) uint64_t skey[kMaxCand];   // sort keys or SelLds
-  __shared__ int32_t sinfo[kMaxCand];
-  __shared__ int32_t sa[kMaxCand];
-  __shared__ int32_t sown[2 * kMaxCand];      // slot owners: Full slots, then quantized slots
+  constexpr int kKeys = ONE_WAY ? CAP : (8 * CAP > (int)sizeof(SelLds) ? CAP : ((int)sizeof(SelLds) + 7) / 8);
+  constexpr int kOwn = 2 * CAP > kPlanSlots * (4 * kMaxSplits + 1) ? 2 * CAP : kPlanSlots * (4 * kMaxSplits + 1);
+  __shared__ __attribute__((aligned(16))) uint64_t skey[kKeys];   // sort keys or SelLds
+  __shared__ int32_t sinfo[CAP];
+  __shared__ int32_t sa[CAP];
+  __shared__ int32_t sown[kOwn];              // slot owners: Full slots, then quantized slots
   __shared__ int32_t tmp[5 * 64 + 16];
   __shared__ int32_t sstat[ST_N];
   int32_t* sb = (int32_t*)skey;               // after the sort: two more int arrays
@@ -687,8 +697,9 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
 
   // a routing batch whose wait for the cache stream timed out leaves the layer as it
   // is: the word is read with the first round of loads and tested before any store
-  const int gate_failed =
-      a.gate_fail ? __hip_atomic_load(a.gate_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  const int32_t* gate = a.gate_fail ? a.gate_fail : counts;
+  const int gate_word = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool gate_failed = a.gate_fail && gate_word;
   if (tid < ST_N) sstat[tid] = 0;
   // ---- one round of loads: the live list carries every candidate's state.
   // Entries are read up to the list's capacity without waiting for its length;
@@ -696,21 +707,23 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
   // range known from the arguments) are read in the same round.
   const int n_aged = U.aged_w1 - U.aged_w0;
   const int ko = (max(G.n_fslots, G.n_qslots) + NT - 1) / NT;   // owner-table slices
-  int spec_ref[PER], spec_aux[PER], spec_win[PER], spec_fo[PER], spec_qo[PER];
-  float spec_sc[PER], spec_aged[PER];
+  int spec_ref[PER] = {}, spec_aux[PER] = {}, spec_win[PER] = {}, spec_fo[PER] = {}, spec_qo[PER] = {};
+  float spec_sc[PER] = {}, spec_aged[PER] = {};
+  // (the loads are unconditional, at clamped indices: a guarded load costs a branch
+  // with its own address arithmetic; what lies past an array's end is not used)
+  const float* aged_sc = a.prefill && n_aged > 0 ? a.init_scores + (int64_t)b * a.n_init : score;
+  const int w_last = n_aged > 0 ? U.aged_w1 - 1 : 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int c = tid + k * NT;
-    const bool ok = !a.prefill && c < G.max_fq;
-    spec_ref[k] = ok ? iref[c] : 0;
-    spec_aux[k] = ok ? iaux[c] : -1;
-    spec_win[k] = ok ? iwin[c] : -1;
-    spec_sc[k] = ok ? iscore[c] : 0.f;
-    spec_fo[k] = k < ko && c < G.n_fslots ? fowner[c] : -1;
-    spec_qo[k] = k < ko && c < G.n_qslots ? qowner[c] : -1;
-    const int w = U.aged_w0 + c;
-    spec_aged[k] = c >= n_aged ? 0.f
-                 : (a.prefill ? a.init_scores[(int64_t)b * a.n_init + w] : score[w]);
+    if (k * NT >= max(max(G.max_fq, n_aged), max(G.n_fslots, G.n_qslots))) break;   // uniform
+    const int c = tid + k * NT, ci = min(c, G.max_fq);   // the lists hold max_fq + 1 entries
+    spec_ref[k] = iref[ci];
+    spec_aux[k] = iaux[ci];
+    spec_win[k] = iwin[ci];
+    spec_sc[k] = iscore[ci];
+    spec_fo[k] = fowner[min(c, G.n_fslots)];             // so do the owner tables
+    spec_qo[k] = qowner[min(c, G.n_qslots)];
+    spec_aged[k] = aged_sc[min(U.aged_w0 + c, w_last)];
   }
   // scores of the windows that follow the routed range (the next steps' recent
   // region; at most NR of them have started)
@@ -726,7 +739,7 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
     if (tid == 0) set_error(counts, ERR_GATE);
     return;
   }
-  if (n_cand > kMaxCand) {
+  if (n_cand > CAP) {
     if (tid == 0) set_error(counts, ERR_CAND);
     return;
   }
@@ -750,7 +763,7 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
   }
   // tier selection, ahead of the barrier: the range of the candidates' upper key
   // words per wave, and cleared first-round counters
-  const bool one_way = (G.flags & 1u) != 0;
+  const bool one_way = ONE_WAY && (G.flags & 1u) != 0;
   SelLds& sel = *reinterpret_cast<SelLds*>(skey);
   if (!one_way) {
     const int lane = tid & 63, wave = tid >> 6;
@@ -832,13 +845,13 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
     // p < K_f + K_q <=> key < thr[2]
     const int target[3] = {G.K_f, G.K_f + half_q, G.K_f + G.K_q};
     uint32_t bel[PER];
-    select_tiers(my_key, kc, n_cand, target, G.bits_cfg == 42 ? 7 : 5, sel, bel);
+    select_tiers<NT, PER>(my_key, kc, n_cand, target, G.bits_cfg == 42 ? 7 : 5, sel, bel);
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int nt = (bel[k] & 1u) ? T_FULL : ((bel[k] & 4u) ? T_QUANT : T_EVICTED);
       my_info[k] = nt | (((bel[k] & 2u) ? 0 : half_q) << 8);
     }
-  } else {
+  } else if constexpr (ONE_WAY) {
     int n_pow = 1;
     while (n_pow < n_cand) n_pow <<= 1;
     __syncthreads();
@@ -933,7 +946,7 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
       fl[3][k] = (my_req[k] & 2) != 0;
       fl[4][k] = fo == -2;
     }
-    flag_scan<5>(fl, rk, tots, tmp, km);
+    flag_scan<NT, PER>(fl, rk, tots, tmp, km);
     nfreeF = tots[0] + tots[4];
     nfreeQ = tots[1];
     nreqF = tots[2];
@@ -1073,7 +1086,6 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
     const int u_hi = (int)((uint32_t)end * (uint32_t)S4 / (uint32_t)total);
     for (int u = u_lo; u <= u_hi; ++u) s_first[u] = next;
   };
-  static_assert(kPlanSlots * (4 * 256 + 1) <= 2 * kMaxCand, "plan slots fit the owner tables");
   __syncthreads();
   {
     bool fl[3][PER];
@@ -1086,7 +1098,7 @@ __global__ __launch_bounds__(kRetierThreads) void k_retier(RetierArgs a) {
       fl[1][k] = in && my_nt[k] == T_QUANT && my_bits[k] == 4;
       fl[2][k] = in && my_nt[k] == T_QUANT && my_bits[k] != 4;
     }
-    flag_scan<3>(fl, rk, tots, tmp, kc);
+    flag_scan<NT, PER>(fl, rk, tots, tmp, kc);
     n_items = tots[0] + tots[1] + tots[2];
     total_live = tots[0] * G.cost_bf16 + tots[1] * G.cost_q4 + tots[2] * G.cost_q2;
     int total[kPlanSlots];   // the planned steps' totals
@@ -1371,7 +1383,16 @@ hipError_t launch_score_pow(const ScorePowArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_retier(const RetierArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_retier, dim3(a.g.B, a.n_units), dim3(kRetierThreads), 0, st, a);
+  // candidates, list entries, slots and ring windows a thread array has to hold
+  int n_aged = 0;
+  for (int i = 0; i < a.n_units; ++i) n_aged = std::max(n_aged, a.unit[i].aged_w1 - a.unit[i].aged_w0);
+  const int need = std::max({(a.prefill ? 0 : a.g.max_fq) + n_aged, a.g.max_fq, a.g.n_fslots, a.g.n_qslots, a.g.NR});
+  const dim3 grid(a.g.B, a.n_units);
+  if (a.g.flags & 1u) hipLaunchKernelGGL((k_retier<1024, 4, true>), grid, dim3(1024), 0, st, a);   // one-way policy
+  else if (need <= 256) hipLaunchKernelGGL((k_retier<256, 1, false>), grid, dim3(256), 0, st, a);
+  else if (need <= 512) hipLaunchKernelGGL((k_retier<512, 1, false>), grid, dim3(512), 0, st, a);
+  else if (need <= 1024) hipLaunchKernelGGL((k_retier<1024, 1, false>), grid, dim3(1024), 0, st, a);
+  else hipLaunchKernelGGL((k_retier<1024, 4, false>), grid, dim3(1024), 0, st, a);
   return hipGetLastError();
 }
 hipError_t launch_manual_move(const RetierArgs& a, int seq, int window, int to_quant, hipStream_t st) {
