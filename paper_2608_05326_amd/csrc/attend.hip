@@ -73,6 +73,40 @@ __device__ __forceinline__ uint32_t code_word(const uint32_t* words, int e, int*
   return words[e / per];
 }
 
+// The 8 codes of entry e.  BITS 4 or 2: the window's width, chosen once per window by
+// a scalar branch around all of its products; BITS 0: chosen per entry (is4).
+template <int BITS>
+__device__ __forceinline__ f16x8 entry_codes(const uint32_t* words, int e, bool is4) {
+  int ee;
+  if constexpr (BITS == 0) {
+    if (is4) {
+      const uint32_t w = code_word<4>(words, e, &ee);
+      return unpack_codes<4>(w, ee);
+    }
+    const uint32_t w = code_word<2>(words, e, &ee);
+    return unpack_codes<2>(w, ee);
+  } else {
+    uint32_t w = code_word<BITS>(words, e, &ee);
+    // the two widths' paths share subexpressions (the words' shifts), which the compiler
+    // would form ahead of the branch between them and hold for every word at once
+    if constexpr (BITS == 2) asm("; 2-bit code word" : "+v"(w));
+    return unpack_codes<BITS>(w, ee);
+  }
+}
+// Runs f(width) for a quantized window: with 32-token windows one straight path per
+// width (70B, 64K: 2896 -> 2876 us a pass; 8B, batch 8: 601 -> 592; the per-entry
+// branches cost scalar work and fence the scheduling).  The 64-token and RoPE kernels
+// sit at 256 registers and spill with two paths (26.6 -> 31.4 and 20.6 -> 35.4 us).
+template <int W, bool ROPE, class F>
+__device__ __forceinline__ void by_width(int kind, F&& f) {
+  if constexpr (W == 32 && !ROPE) {
+    if (kind == KIND_Q4) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, 2>{});
+  } else {
+    f(std::integral_constant<int, 0>{});
+  }
+}
+
 struct WaveState {
   float m, l;      // running max (log2 domain) and sum for head r of this lane
   f32x4 o[8];      // O rows 4*qg + v, channels 16*cb + r
@@ -85,22 +119,30 @@ struct WaveState {
 // and most windows skip the rescale.
 constexpr float kRescaleSlack = 8.0f;
 
-template <int TB, int NHS>
+// TOK: rows of the tiles that hold tokens of a full window (an 8-token window's single
+// tile is always masked)
+template <int TB, int NHS, int TOK = 16 * TB>
 __device__ __forceinline__ void softmax_window(const f32x4 (&acc)[TB], float bias, int ntok,
                                                float scale_log2, int qg, WaveState& st,
                                                float (&p)[TB][4], float* m_out, float* l_out) {
   float x[TB][4];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[tb][v] = (acc[tb][v] + bias) * scale_log2;
+  if (ntok < TOK) {   // a partial window (scalar branch)
+    int t0 = 4 * qg;
+    asm("; token" : "+v"(t0));   // (the compiler would keep every token number across the loop)
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[tb][v] = t0 + 16 * tb + v < ntok ? x[tb][v] : -INFINITY;
+  }
   float mw = -INFINITY;
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int t = 16 * tb + 4 * qg + v;
-      float y = (acc[tb][v] + bias) * scale_log2;
-      y = t < ntok ? y : -INFINITY;
-      x[tb][v] = y;
-      mw = fmaxf(mw, y);
-    }
+    for (int v = 0; v < 4; ++v) mw = fmaxf(mw, x[tb][v]);
   mw = rows_max(mw);
   if (__builtin_amdgcn_ballot_w64(mw > st.m + kRescaleSlack) != 0) {
     const float m_new = fmaxf(st.m, mw);
@@ -695,7 +737,8 @@ __device__ __forceinline__ void qk_rope_quant(const ItemInfo& in, const KHalf<W,
     const int j = 16 * tb + r;   // token offset in the window
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-      f16x8 ca, cb;   // codes of channels 32 kb + 8 qg + i and their partners + 64
+      // codes of channels 32 kb + 8 qg + i and their partners + 64
+      f16x8 ca, cb;
       int ee;
       if (is4) {
         ca = unpack_codes<4>(code_word<4>(kw, tb * 4 + kb, &ee), ee);
@@ -793,7 +836,6 @@ __device__ __forceinline__ void process_k(const ItemInfo& in, KHalf<W, ROPE>& kh
   } else {
     // ---- quantized window: int4 or int2 codes ----
     constexpr int NC = key_code_regs<W>();
-    const bool is4 = in.kind == KIND_Q4;
     uint32_t kw[4 * NC];
 #pragma unroll
     for (int m = 0; m < NC; ++m)
@@ -884,25 +926,20 @@ __device__ __forceinline__ void process_k(const ItemInfo& in, KHalf<W, ROPE>& kh
       qlo[kb] = __builtin_bit_cast(f16x8, ld16(qlds + qst_off(1, kb, lane)));
     }
     }
+    auto products = [&](auto bits) {
+      constexpr int BITS = decltype(bits)::value;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      acc[tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int tb = 0; tb < TB; ++tb) {
+        acc[tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        const int e = tb * 4 + kb;
-        int ee;
-        f16x8 cv;
-        if (is4) {
-          uint32_t w = code_word<4>(kw, e, &ee);
-          cv = unpack_codes<4>(w, ee);
-        } else {
-          uint32_t w = code_word<2>(kw, e, &ee);
-          cv = unpack_codes<2>(w, ee);
+        for (int kb = 0; kb < 4; ++kb) {
+          const f16x8 cv = entry_codes<BITS>(kw, tb * 4 + kb, in.kind == KIND_Q4);
+          acc[tb] = mfma_f16(cv, qhi[kb], acc[tb]);
+          acc[tb] = mfma_f16(cv, qlo[kb], acc[tb]);
         }
-        acc[tb] = mfma_f16(cv, qhi[kb], acc[tb]);
-        acc[tb] = mfma_f16(cv, qlo[kb], acc[tb]);
       }
-    }
+    };
+    by_width<W, ROPE>(in.kind, products);
     softmax_window<TB, NHS>(acc, bias, ntok, G.scale_log2, qg, st, p_, m_w, l_w);
   }
 }
@@ -992,7 +1029,7 @@ __device__ __forceinline__ void process_v8(const ItemInfo& in, VHalf<8>& vh, Wav
 // P.V of one window into the running output, then the window's statistics.
 // The open window takes this step's value (and stores it); tokens past the end
 // of a partial window contribute nothing.
-template <int W, int NHS>
+template <int W, int NHS, bool ROPE>
 __device__ __forceinline__ void process_v(const ItemInfo& in, VHalf<W>& vh, WaveState& st,
                                           const float (&p_)[row_tiles<W>()][4], float m_w, float l_w,
                                           const AttnArgs& a, int b, int g, int qg, int r,
@@ -1008,6 +1045,8 @@ __device__ __forceinline__ void process_v(const ItemInfo& in, VHalf<W>& vh, Wave
   if (in.kind == KIND_BF16) {
     if (ntok < W || in.open) {
       const int pos = ntok - 1;
+      int qt = qg;
+      asm("; token group" : "+v"(qt));   // (as in softmax_window)
       if (in.open) {
         const uint16_t* vn = a.v_new + ((int64_t)b * G.H_kv + g) * kHeadDim;
         uint8_t* pw = const_cast<uint8_t*>(in.p);
@@ -1034,7 +1073,7 @@ __device__ __forceinline__ void process_v(const ItemInfo& in, VHalf<W>& vh, Wave
       for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const bool lo_ok = v_tok(kt, qg, 2 * i) < ntok, hi_ok = v_tok(kt, qg, 2 * i + 1) < ntok;
+          const bool lo_ok = v_tok(kt, qt, 2 * i) < ntok, hi_ok = v_tok(kt, qt, 2 * i + 1) < ntok;
           const uint32_t mask = (lo_ok ? 0x0000FFFFu : 0u) | (hi_ok ? 0xFFFF0000u : 0u);
 #pragma unroll
           for (int cb = 0; cb < 8; ++cb) vh.d[kt * 8 + cb][i] &= mask;
@@ -1052,47 +1091,43 @@ __device__ __forceinline__ void process_v(const ItemInfo& in, VHalf<W>& vh, Wave
   } else {
     constexpr int NC = key_code_regs<W>();   // (8-token windows take process_v8)
     constexpr int NG = kHeadDim / W;
-    const bool is4 = in.kind == KIND_Q4;
     uint32_t vw[4 * NC];
 #pragma unroll
     for (int m = 0; m < NC; ++m)
 #pragma unroll
       for (int i = 0; i < 4; ++i) vw[4 * m + i] = vh.d[m][i];
+    auto products = [&](auto bits) {
+      constexpr int BITS = decltype(bits)::value;
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      f16x8 pv;
+      for (int kt = 0; kt < KT; ++kt) {
+        f16x8 pv;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pv[j] = (_Float16)p_[2 * kt + (j >> 2)][j & 3];
+        for (int j = 0; j < 8; ++j) pv[j] = (_Float16)p_[2 * kt + (j >> 2)][j & 3];
 #pragma unroll
-      for (int cb = 0; cb < 8; ++cb) {
-        const int e = kt * 8 + cb;
-        const int vg = (16 * cb) / W;
-        int ee;
-        f16x8 cv;
-        if (is4) {
-          uint32_t w = code_word<4>(vw, e, &ee);
-          cv = unpack_codes<4>(w, ee);
-        } else {
-          uint32_t w = code_word<2>(vw, e, &ee);
-          cv = unpack_codes<2>(w, ee);
+        for (int cb = 0; cb < 8; ++cb) {
+          const int e = kt * 8 + cb;
+          const int vg = (16 * cb) / W;
+          const f16x8 cv = entry_codes<BITS>(vw, e, in.kind == KIND_Q4);
+          const u32x4 sv4 = vh.d[NC + (kt * NG + vg) * 2];
+          const u32x4 zv4 = vh.d[NC + 1 + (kt * NG + vg) * 2];
+          f16x8 vv;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            // vector elements go through scalars: bit-casting an element of an
+            // ext_vector directly reads element 0 with this compiler
+            const uint32_t si = sv4[i], zi = zv4[i];
+            f16x2 c2 = {cv[2 * i], cv[2 * i + 1]};
+            f16x2 r2 = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, si), c2,
+                                                 __builtin_bit_cast(f16x2, zi));
+            vv[2 * i] = r2[0];
+            vv[2 * i + 1] = r2[1];
+          }
+          st.o[cb] = mfma_f16(pv, vv, st.o[cb]);
+
         }
-        const u32x4 sv4 = vh.d[NC + (kt * NG + vg) * 2];
-        const u32x4 zv4 = vh.d[NC + 1 + (kt * NG + vg) * 2];
-        f16x8 vv;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // vector elements go through scalars: bit-casting an element of an
-          // ext_vector directly reads element 0 with this compiler
-          const uint32_t si = sv4[i], zi = zv4[i];
-          f16x2 c2 = {cv[2 * i], cv[2 * i + 1]};
-          f16x2 r2 = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, si), c2,
-                                               __builtin_bit_cast(f16x2, zi));
-          vv[2 * i] = r2[0];
-          vv[2 * i + 1] = r2[1];
-        }
-        st.o[cb] = mfma_f16(pv, vv, st.o[cb]);
       }
-    }
+    };
+    by_width<W, ROPE>(in.kind, products);
   }
   if (qg == 0 && r < gqa) mref[(int64_t)in.it * G.H_q + g * gqa + r] = make_float2(m_w, l_w);
 }
@@ -1369,11 +1404,18 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
     merge_streams(st, qg, r);
   } else {
     for (int it = first; it < last; ++it) {
-      const ItemInfo ia = info(it);
+      ItemInfo ia = info(it);
+      if constexpr (W == 32 && !ROPE) {
+        // one item per wave: scalar branches on its kind (as a vector value every code
+        // expansion sits between two masked branches, one per bit width)
+        ia.kind = __builtin_amdgcn_readfirstlane(ia.kind);
+        ia.ntok = __builtin_amdgcn_readfirstlane(ia.ntok);
+        ia.open = __builtin_amdgcn_readfirstlane((int)ia.open) != 0;
+      }
       fetch_k<W, ROPE, use_reg_qs<W, NHS, ROPE>()>(ia, KA, lane, r, G);
       fetch_v<W>(ia, V, lane, qg, G);
       process_k<W, NHS, ROPE>(ia, KA, st, qop, qf, qlds, a, b, g, lane, qg, r, p_, &m_w, &l_w);
-      process_v<W, NHS>(ia, V, st, p_, m_w, l_w, a, b, g, qg, r, mref);
+      process_v<W, NHS, ROPE>(ia, V, st, p_, m_w, l_w, a, b, g, qg, r, mref);
     }
   }
 
