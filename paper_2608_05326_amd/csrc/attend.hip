@@ -360,19 +360,18 @@ __device__ __forceinline__ void dma16(const void* g, uint8_t* lds_row) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_row, 16, 0, 0);
 }
 
-// bytes of the item's record: a bf16 window (keys then values), or a quantized
-// record (key codes, value codes, key scale / zero, value scale / zero)
-template <int W>
-__device__ __forceinline__ int slot_record_bytes(const ItemInfo& in, const Geometry& G) {
-  return in.kind == KIND_BF16 ? 2 * W * kHeadDim * 2 : (int)G.qrec_bytes;
-}
-
+// Starts the loads of an item's record into its slot: a bf16 window (keys then
+// values) is four full rows of 1 KiB, a quantized record (key codes, value codes, key
+// scale / zero, value scale / zero) one full row and part of a second (at most 1664
+// bytes, at least 1056).
 __device__ __forceinline__ void issue_record(const ItemInfo& in, uint8_t* dst, int lane, const Geometry& G) {
-  const int n = slot_record_bytes<8>(in, G);
+  const uint8_t* p = in.p + lane * 16;
+  dma16(p, dst);
+  if (in.kind == KIND_BF16) {   // uniform
 #pragma unroll
-  for (int row = 0; row < kPairSlot / 1024; ++row) {
-    if (row * 1024 >= n) break;   // uniform
-    if (row * 1024 + lane * 16 < n) dma16(in.p + row * 1024 + lane * 16, dst + row * 1024);
+    for (int row = 1; row < kPairSlot / 1024; ++row) dma16(p + row * 1024, dst + row * 1024);
+  } else if (lane * 16 < (int)G.qrec_bytes - 1024) {
+    dma16(p + 1024, dst + 1024);
   }
 }
 
@@ -1305,6 +1304,17 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
     run_ref = i < last && i < n_fq ? iref[i] : 0;
   }
 
+  // pairs of 8-token windows: the run's first 64 list refs, one per lane
+  int refs = 0;
+  if constexpr (SLOT) {
+    if (plan_ok) {
+      const int a6 = __shfl(rec, lane + 2, 64), b6 = __shfl(run_ref, lane - kPlanRefs, 64);
+      refs = lane < kPlanRefs ? a6 : b6;
+    } else if (first + lane < min(last, n_fq)) {
+      refs = s_ref[first + lane];
+    }
+  }
+
   WaveState st;
   st.m = -INFINITY;
   st.l = 0.f;
@@ -1316,7 +1326,8 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
   uint8_t* qpool = ub + a.L.qpool;
   uint8_t* ring = ub + a.L.ring;
   uint8_t* sinkp = ub + a.L.sinkp;
-  auto info = [&](int it) {
+  // item `it` of the run; `ref`: its list reference (live-list items)
+  auto describe = [&](int it, int32_t ref) {
     ItemInfo in;
     in.it = it;
     in.kind = KIND_BF16;
@@ -1325,16 +1336,6 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
     in.win = -1;
     if (it < n_fq) {
       if constexpr (ROPE) in.win = iwin_l[it];
-      int32_t ref;
-      if (plan_ok) {
-        const int k = it - first;
-        ref = k < kPlanRefs        ? __builtin_amdgcn_readlane(rec, 2 + k)
-              : k < kPlanRefs + 64 ? __builtin_amdgcn_readlane(run_ref, k - kPlanRefs)
-                                   : iref[it];
-      } else {
-        ref = s_ref[it];
-      }
-      ref = __builtin_amdgcn_readfirstlane(ref);   // one item per wave: scalar branches on its kind
       in.kind = ref >> 28;
       const int64_t slot = ref & 0x0FFFFFFF;
       in.p = in.kind == KIND_BF16 ? fpool + slot * G.fslot_bytes + g * G.fhead_bytes
@@ -1351,6 +1352,48 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
     }
     return in;
   };
+  // pairs of 8-token windows: the run's first 64 items, one per lane (address, and
+  // kind | tokens << 4 | open << 8), so that an item costs three lane reads in the loop
+  int t_meta = 0, t_lo = 0, t_hi = 0;
+  if constexpr (SLOT) {
+    if (first + lane < last) {
+      const ItemInfo x = describe(first + lane, refs);
+      t_meta = x.kind | (x.ntok << 4) | (x.open ? 256 : 0);
+      const uint64_t ad = (uint64_t)x.p;
+      t_lo = (int)(uint32_t)ad;
+      t_hi = (int)(uint32_t)(ad >> 32);
+    }
+  }
+  auto info = [&](int it) {
+    const int k = it - first;
+    if constexpr (SLOT) {
+      // (the rare path ends in a scalar: a load that only reached its wait at the join
+      // would make every item wait for all memory operations, stores among them)
+      if (k >= 64) return describe(it, it < n_fq ? __builtin_amdgcn_readfirstlane(iref[it]) : 0);
+      ItemInfo in;
+      const int m = __builtin_amdgcn_readlane(t_meta, k);
+      const uint32_t lo = __builtin_amdgcn_readlane(t_lo, k), hi = __builtin_amdgcn_readlane(t_hi, k);
+      in.p = (const uint8_t*)(((uint64_t)hi << 32) | lo);
+      in.it = it;
+      in.win = -1;
+      in.kind = m & 15;
+      in.ntok = (m >> 4) & 15;
+      in.open = (m & 256) != 0;
+      return in;
+    } else {
+      int32_t ref = 0;
+      if (it < n_fq) {
+        if (plan_ok)
+          ref = k < kPlanRefs        ? __builtin_amdgcn_readlane(rec, 2 + k)
+                : k < kPlanRefs + 64 ? __builtin_amdgcn_readlane(run_ref, k - kPlanRefs)
+                                     : iref[it];
+        else
+          ref = s_ref[it];
+        ref = __builtin_amdgcn_readfirstlane(ref);   // one item per wave: scalar branches on its kind
+      }
+      return describe(it, ref);
+    }
+  };
 
   // ---- window loop: this wave's contiguous run of windows ----
   constexpr int TB = row_tiles<W>();
@@ -1362,7 +1405,7 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
     // pairs of windows through the wave's LDS slot: wait for the pair, gather its
     // operands, start the next pair's loads into the slot, then compute
     __shared__ __attribute__((aligned(16))) uint8_t s_slots[4 * 2 * kPairSlot];
-    uint8_t* slot = s_slots + wave * 2 * kPairSlot;
+    uint8_t* slot = s_slots + __builtin_amdgcn_readfirstlane(wave) * 2 * kPairSlot;
     mo_base = s_slots;
     // the pair starting at item i: its second item, and whether it has one
     auto pair_at = [&](int i, ItemInfo& x, ItemInfo& y) {
@@ -1375,15 +1418,26 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
       bool pb = pair_at(first, ia, ib);
       issue_record(ia, slot, lane, G);
       if (pb) issue_record(ib, slot + kPairSlot, lane, G);
-      f16x8 qhi[4], qlo[4];
-      float bias;
-      for (int it = first; it < last;) {
-        const int nxt = it + (pb ? 2 : 1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        read_pair(ia.kind, pb, slot, KA, V, qhi, qlo, &bias, qop, r, qg, G);
+      // The loop is bound by instruction issue (about 700 per pair against 2.6 KiB of
+      // loads), so what a pair does not need is kept out of it: each kind of pair, and
+      // a window without a partner, has a straight path of its own (no branches between
+      // the entries, no selects for an absent window); items are described by three
+      // lane reads; nothing waits for the statistics store.  32K context, 8 KV heads of
+      // 4 query heads, 2269 live int2 and bf16 windows: 22.1 -> 19.4 us a launch.  Three
+      // workgroups per compute unit (the registers would allow it) with 96 splits give
+      // 0.6 us here and lose 0.4 us in the merge.
+      auto pass = [&](auto kind_c, auto two_c, int it) {
+        constexpr int KIND = decltype(kind_c)::value;
+        constexpr bool TWO = decltype(two_c)::value;
+        const int nxt = it + (TWO ? 2 : 1);
+        f16x8 qhi[4], qlo[4];
+        float bias;
+        read_pair(KIND, TWO, slot, KA, V, qhi, qlo, &bias, qop, r, qg, G);
         wave_sync_lds();
-        if (ia.open) patch_open8(ia, 0, KA, V, a, b, g, qg, r);
-        if (pb && ib.open) patch_open8(ib, 1, KA, V, a, b, g, qg, r);
+        if constexpr (KIND == KIND_BF16) {
+          if (ia.open) patch_open8(ia, 0, KA, V, a, b, g, qg, r);
+          if (TWO && ib.open) patch_open8(ib, 1, KA, V, a, b, g, qg, r);
+        }
         ItemInfo na, nb;
         const bool has = nxt < last;
         const bool npb = pair_at(has ? nxt : it, na, nb) && has;
@@ -1393,12 +1447,26 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
         }
         __builtin_amdgcn_sched_barrier(0);
         float lw;
-        pair_k(ia.kind, pb, ia.ntok, ib.ntok, KA, qop, qhi, qlo, bias, G.scale_log2, qg, r, st, p_[0], &lw);
-        pair_v(ia.kind, pb, ia.it, ib.it, ia.ntok, ib.ntok, V, st, p_[0], lw, a, g, qg, r, mref);
+        // (a quantized window is complete)
+        const int ntA = KIND == KIND_BF16 ? ia.ntok : 8, ntB = KIND == KIND_BF16 ? ib.ntok : 8;
+        pair_k(KIND, TWO, ntA, ntB, KA, qop, qhi, qlo, bias, G.scale_log2, qg, r, st, p_[0], &lw);
+        pair_v(KIND, TWO, ia.it, ib.it, ntA, ntB, V, st, p_[0], lw, a, g, qg, r, mref);
         ia = na;
         ib = nb;
         pb = npb;
-        it = nxt;
+        return nxt;
+      };
+      for (int it = first; it < last;) {
+        // the pair's slot loads; the statistics store of the pair before, issued after
+        // them, may still be on its way (memory operations complete in order)
+        if (it == first) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+        auto by_kind = [&](auto two) {
+          if (ia.kind == KIND_BF16) return pass(std::integral_constant<int, KIND_BF16>{}, two, it);
+          if (ia.kind == KIND_Q4) return pass(std::integral_constant<int, KIND_Q4>{}, two, it);
+          return pass(std::integral_constant<int, KIND_Q2>{}, two, it);
+        };
+        it = pb ? by_kind(std::true_type{}) : by_kind(std::false_type{});
       }
     }
     merge_streams(st, qg, r);

@@ -377,8 +377,8 @@ hipError_t timed(qevict_cache* c, int kernel, hipStream_t st, F&& launch, int un
 // leaves free, and the queue-level wait, whose stall of the cache stream (about
 // 12 us a batch) gives it that room, was measured faster: 128K context with
 // 64-token windows (256-register attention), the RoPE-aware tier (256), GQA 8
-// (217 plus an 80-register migration wave), 8-token windows (222) with 16
-// layer caches.
+// (228 plus an 80-register migration wave), 8-token windows with 16 layer
+// caches.
 hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
   int av = 0, mv = 0;
   size_t al = 0, ml = 0;
@@ -386,12 +386,10 @@ hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
   if (e == hipSuccess) e = migrate_footprint(g, &mv, &ml);
   if (e != hipSuccess) return e;
   auto granule = [](int v) { return (v + 7) / 8 * 8; };   // VGPR allocation granule
-  // A migration wave counts as 72 registers at least: that of 8-token windows needs
-  // fewer (53) and would fit, but there the better order depends on the number of
-  // layer caches (gate / queue-level wait: 28.6 / 30.4 us a step with 4, 31.2 / 30.7
-  // with 16), so those keep the queue-level wait.
-  constexpr int kLeastMigrate = 72;
-  *fits = 2 * granule(av) + std::max(granule(mv), kLeastMigrate) <= 512 && 2 * al + ml <= 160 * 1024;
+  // (with 8-token windows all three would fit, but there the better order depends on
+  // the number of layer caches -- gate / queue-level wait: 28.6 / 30.4 us a step with
+  // 4, 31.2 / 30.7 with 16 -- so those keep the queue-level wait)
+  *fits = g.W != 8 && 2 * granule(av) + granule(mv) <= 512 && 2 * al + ml <= 160 * 1024;
   return hipSuccess;
 }
 
