@@ -1418,8 +1418,8 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
       bool pb = pair_at(first, ia, ib);
       issue_record(ia, slot, lane, G);
       if (pb) issue_record(ib, slot + kPairSlot, lane, G);
-      // The loop is bound by instruction issue (about 700 per pair against 2.6 KiB of
-      // loads), so what a pair does not need is kept out of it: each kind of pair, and
+      // The loop is bound by instruction issue (several hundred a pair against 2.2 KiB
+      // of int2 loads), so what a pair does not need is kept out: each kind of pair, and
       // a window without a partner, has a straight path of its own (no branches between
       // the entries, no selects for an absent window); items are described by three
       // lane reads; nothing waits for the statistics store.  32K context, 8 KV heads of

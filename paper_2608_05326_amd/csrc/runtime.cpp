@@ -376,7 +376,7 @@ hipError_t timed(qevict_cache* c, int kernel, hipStream_t st, F&& launch, int un
 // attention.  Where it does not fit it waits for compute units that attention
 // leaves free, and the queue-level wait, whose stall of the cache stream (about
 // 12 us a batch) gives it that room, was measured faster: 128K context with
-// 64-token windows (256-register attention), the RoPE-aware tier (256), GQA 8
+// 64-token windows (246-register attention), the RoPE-aware tier (256), GQA 8
 // (228 plus an 80-register migration wave), 8-token windows with 16 layer
 // caches.
 hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
