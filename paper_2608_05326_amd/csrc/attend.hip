@@ -1575,8 +1575,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
     // ---- output of head h: thread (c4, grp) owns channels 4c4..4c4+3 of splits grp + 8i ----
     const int h = blk;
     const int c4 = tid & 31, grp = tid >> 5;
-    // rounds of NSPT rows a thread (one round with at most 8 NSPT splits); rows past
-    // the last split are read again and not used
+    // rounds of NSPT rows a thread (one round with at most 8 NSPT splits); a row past
+    // the last split reads that one again and becomes zeros (its weight is 0, but 0
+    // times an infinite partial would be NaN)
     auto stat = [&](int sp) {
       float2 v = pml[(int64_t)h * S + min(sp, S - 1)];
       v.x = sp < S ? v.x : -INFINITY;
@@ -1587,7 +1588,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < NSPT; ++i) {
       const int sp = grp + kSplitGroups * i;
-      o[i] = *(const float4*)(part + ((int64_t)h * S + min(sp, S - 1)) * kHeadDim + 4 * c4);
+      const float4 x = *(const float4*)(part + ((int64_t)h * S + min(sp, S - 1)) * kHeadDim + 4 * c4);
+      const bool ok = sp < S;
+      o[i] = make_float4(ok ? x.x : 0.f, ok ? x.y : 0.f, ok ? x.z : 0.f, ok ? x.w : 0.f);
       ml[i] = stat(sp);
     }
     float m = -INFINITY;
