@@ -102,7 +102,8 @@ __device__ __forceinline__ void obs_chunk(const ObsArgs& a, const u32x4 (&kop)[2
   // outputs of this lane: the chunk's max (lanes lh = 0) or exp-sum (lh = 1), and the
   // sum of window lh of the chunk (W = 32) or of the one window (W = 64, lh = 0)
   float* const ml_out = (lh ? a.cl : a.cm) + (bg * a.n_chunks + c) * n_rows + r0;
-  float* const wl_out = a.wl + (bg * a.n_w + w0 + (wpc == 2 ? lh : 0)) * n_rows + r0;
+  float* const wl_c = a.wl + (bg * a.n_w + w0) * n_rows + r0;
+  float* const wl_out = wl_c + (wpc == 2 && lh ? n_rows : 0);
   const bool has_w = w0 >= 0 && (wpc == 2 ? w0 + lh < a.n_w : lh == 0 && w0 < a.n_w);
   // the query operands of a row tile are read while the tile before is reduced
   u32x4 q[8];
@@ -174,21 +175,25 @@ __device__ __forceinline__ void obs_chunk(const ObsArgs& a, const u32x4 (&kop)[2
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const float s = pair_sums(l8[2 * j], l8[2 * j + 1]);
-        const int w = w0 + 2 * j + lh;
-        if (row < nr && w >= 0 && w < a.n_w) a.wl[(bg * a.n_w + w) * n_rows + r0 + row] = s;
+        const int w = 2 * j + lh;   // of the chunk's eight
+        if (row < nr && w0 >= 0 && w0 + w < a.n_w) wl_c[(uint32_t)(w * n_rows + row)] = s;
       }
     }
   }
 }
 
-// The workgroups of a (sequence, KV head) are resident together (one of eight waves
-// per compute unit), stage up to 512 query rows once and go through the chunks: wave
-// v of them takes chunks v, v + NV, ..., and while it computes one the keys of the
-// next are on their way into a second set of registers.  With a workgroup per four
-// chunks (keys loaded, then used) all workgroups of the chip loaded at once and then
-// computed at once: 213 -> 194 us at 8 x 512 rows x 2048 chunks (128K; 268 MB of keys,
-// 137 GFLOP), 226 -> 184 us at 32 x 256 rows x 1024 chunks (four 64K prompts, 537 MB),
-// 40.6 -> 38.6 us at 8 x 128 rows x 1024 chunks (64K).
+// One workgroup of eight waves per compute unit: it stages up to 512 query rows of a
+// (sequence, KV head) once and its waves go through the chunks in turn; while a wave
+// computes one the keys of its next are on their way into a second set of registers.  With a workgroup per four chunks (keys loaded, then used) all
+// workgroups of the chip loaded at once and then computed at once: 213 -> 194 us at
+// 8 x 512 rows x 2048 chunks (128K; 268 MB of keys, 137 GFLOP), 226 -> 184 us at
+// 32 x 256 rows x 1024 chunks (four 64K prompts, 537 MB), 40.6 -> 38.6 us at 8 x 128
+// rows x 1024 chunks (64K).
+// The chunks of all (sequence, KV head) pairs are one list of which every workgroup
+// takes an equal contiguous part (staging the next pair's rows where it crosses one):
+// a whole number of workgroups per pair left compute units without work (136 pairs
+// on 256) or ran a second, nearly empty wave of workgroups (264).  Parts of whole
+// rounds of eight chunks are not equal enough: 78 -> 82 us at 8 pairs x 625 chunks.
 // 32x32 tiles halve the cross-lane work of 16x16 ones: a row's 64 logits lie in two
 // lanes instead of four, one lane exchange serves both window sums, and a tile's
 // masks, addresses and stores serve 32 rows.
@@ -198,47 +203,56 @@ __device__ __forceinline__ void obs_chunk(const ObsArgs& a, const u32x4 (&kop)[2
 // one tile with the exponentials of the other within a wave changed nothing.
 // W8: 8-token windows (eight per chunk), a separate instantiation so the other window
 // sizes carry none of it
+constexpr int kObsWaves = kObsThreads / 64;
+constexpr int kObsUnits = 256;         // compute units (and resident workgroups)
 template <bool W8>
 __global__ __launch_bounds__(kObsThreads, 1) void k_obs_chunks(ObsArgs a) {
-  const int g = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nv = gridDim.x * (kObsThreads / 64);
-  const int v = wave * gridDim.x + blockIdx.x;   // (waves of different workgroups first: an even share)
-  const int64_t bg = (int64_t)b * a.H_kv + g;
   __shared__ __attribute__((aligned(16))) uint8_t sq[kObsRows * kObsRowBytes];
-  const uint16_t* kb = a.k + bg * a.T * kHeadDim;
-  const uint16_t* qb = a.q + ((int64_t)b * a.H_q + (int64_t)g * a.gqa) * a.n_obs * kHeadDim;
-  auto load = [&](int c, u32x4 (&kop)[2][8]) {
+  const int64_t total = (int64_t)a.n_chunks * a.B * a.H_kv;   // (2^31 chunks of keys exceed any memory)
+  const int begin = (int)(total * blockIdx.x / gridDim.x), end = (int)(total * (blockIdx.x + 1) / gridDim.x);
+  for (int at = begin; at < end;) {
+    const int pair = __builtin_amdgcn_readfirstlane(at / a.n_chunks);
+    const int64_t bg = pair;
+    // the pair's chunks [c0, c_end) of this part; the wave after the one that took the
+    // part's last chunk so far takes the first
+    const int c0 = at - pair * a.n_chunks, c_end = min(c0 + end - at, a.n_chunks);
+    const int c_first = c0 + ((wave - (at - begin)) & (kObsWaves - 1));
+    at += c_end - c0;
+    const uint16_t* kb = a.k + bg * a.T * kHeadDim;
+    const uint16_t* qb = a.q + bg * a.gqa * a.n_obs * kHeadDim;   // (H_q = H_kv * gqa)
+    auto load = [&](int c, u32x4 (&kop)[2][8]) {
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const int key = a.cbase + kObsChunkKeys * c + 32 * kt + (lane & 31);
-      // (keys outside the prompt are masked: any key in their place)
-      const uint16_t* p = kb + (int64_t)max(min(key, a.T - 1), 0) * kHeadDim + 8 * (lane >> 5);
+      for (int kt = 0; kt < 2; ++kt) {
+        const int key = a.cbase + kObsChunkKeys * c + 32 * kt + (lane & 31);
+        // (keys outside the prompt are masked: any key in their place)
+        const uint16_t* p = kb + (int64_t)max(min(key, a.T - 1), 0) * kHeadDim + 8 * (lane >> 5);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) kop[kt][ks] = *(const u32x4*)(p + 16 * ks);
-    }
-  };
-  u32x4 k0[2][8], k1[2][8];
-  for (int r0 = 0; r0 < a.n_rows; r0 += kObsRows) {
-    const int nr = min(kObsRows, a.n_rows - r0), nr32 = (nr + 31) & ~31;
-    int c = v;
-    if (c < a.n_chunks) load(c, k0);
-    __syncthreads();   // the previous rows are consumed
+        for (int ks = 0; ks < 8; ++ks) kop[kt][ks] = *(const u32x4*)(p + 16 * ks);
+      }
+    };
+    u32x4 k0[2][8], k1[2][8];
+    for (int r0 = 0; r0 < a.n_rows; r0 += kObsRows) {
+      const int nr = min(kObsRows, a.n_rows - r0), nr32 = (nr + 31) & ~31;
+      int c = c_first;
+      if (c < c_end) load(c, k0);
+      __syncthreads();   // the previous rows are consumed
 #pragma unroll 4
-    for (int e = tid; e < nr32 * 16; e += kObsThreads) {
-      const int row = e >> 4, part = e & 15;
-      const u32x4 x = row < nr ? *(const u32x4*)(qb + (int64_t)(r0 + row) * kHeadDim + 8 * part)
-                               : (u32x4){0, 0, 0, 0};
-      *(u32x4*)(sq + row * kObsRowBytes + 16 * part) = x;
-    }
-    __syncthreads();
-    for (; c < a.n_chunks; c += 2 * nv) {
-      const int c1 = c + nv, c2 = c1 + nv;
-      if (c1 < a.n_chunks) load(c1, k1);
-      obs_chunk<W8>(a, k0, sq, c, bg, r0, nr, lane);
-      if (c1 < a.n_chunks) {
-        if (c2 < a.n_chunks) load(c2, k0);
-        obs_chunk<W8>(a, k1, sq, c1, bg, r0, nr, lane);
+      for (int e = tid; e < nr32 * 16; e += kObsThreads) {
+        const int row = e >> 4, part = e & 15;
+        const u32x4 x = row < nr ? *(const u32x4*)(qb + (int64_t)(r0 + row) * kHeadDim + 8 * part)
+                                 : (u32x4){0, 0, 0, 0};
+        *(u32x4*)(sq + row * kObsRowBytes + 16 * part) = x;
+      }
+      __syncthreads();
+      for (; c < c_end; c += 2 * kObsWaves) {
+        const int c1 = c + kObsWaves, c2 = c1 + kObsWaves;
+        if (c1 < c_end) load(c1, k1);
+        obs_chunk<W8>(a, k0, sq, c, bg, r0, nr, lane);
+        if (c1 < c_end) {
+          if (c2 < c_end) load(c2, k0);
+          obs_chunk<W8>(a, k1, sq, c1, bg, r0, nr, lane);
+        }
       }
     }
   }
@@ -481,14 +495,16 @@ __global__ __launch_bounds__(256) void k_obs_windows(ObsArgs a, int wpw) {
 
 hipError_t launch_prefill_scores(const ObsArgs& a, hipStream_t st) {
   if (a.n_w <= 0) return hipSuccess;
-  constexpr int kUnits = 256, kWaves = kObsThreads / 64, kOnceWaves = 16 * kUnits, kOnceMaxRows = 64;
-  if ((int64_t)a.n_chunks * a.H_kv * a.B <= kOnceWaves || a.n_rows <= kOnceMaxRows) {
+  constexpr int kOnceWaves = 16 * kObsUnits, kOnceMaxRows = 64, kOnceMaxChunks = 8;
+  if ((int64_t)a.n_chunks * a.H_kv * a.B <= kOnceWaves || a.n_rows <= kOnceMaxRows || a.n_chunks <= kOnceMaxChunks) {
     const dim3 grid((a.n_chunks + 3) / 4, a.H_kv, a.B);
     if (a.W == 8) hipLaunchKernelGGL(k_obs_chunks_once<true>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(k_obs_chunks_once<false>, grid, dim3(256), 0, st, a);
-  } else {   // one workgroup per compute unit over the whole grid
-    const int share = std::max(1, kUnits / (a.H_kv * a.B));
-    const dim3 grid(std::min(share, (a.n_chunks + kWaves - 1) / kWaves), a.H_kv, a.B);
+  } else {   // (more than 4096 chunks: two or more a wave)
+    // A whole number of workgroups per pair where they fill 15 of 16 units (none then
+    // crosses from pair to pair: 92 -> 87 us at 12 pairs x 384 rows x 625 chunks).
+    const int64_t pairs = (int64_t)a.H_kv * a.B, whole = kObsUnits / pairs * pairs;
+    const dim3 grid((unsigned)(16 * whole >= 15 * kObsUnits ? whole : kObsUnits));
     if (a.W == 8) hipLaunchKernelGGL(k_obs_chunks<true>, grid, dim3(kObsThreads), 0, st, a);
     else hipLaunchKernelGGL(k_obs_chunks<false>, grid, dim3(kObsThreads), 0, st, a);
   }
