@@ -270,11 +270,14 @@ __device__ __forceinline__ f32x4 mfma_obs16(bf16x8 a, bf16x8 b, f32x4 c) {
 // 512 chunks (32K), 6.2 against 7.4 at 8 x 32 rows x 33 chunks (2K), 42.7 against 45.0
 // (all three launches) at 8 x 32 rows x 1024 chunks (64K).
 // four workgroups per compute unit (at most 128 VGPRs); W8: 8-token windows (eight
-// per chunk), a separate instantiation so the other window sizes carry none of it
+// per chunk), a separate instantiation so the other window sizes carry none of it.
+// That one holds its chunk's addresses in scalar registers (a scalar wave number) and
+// each exponential once: with 9 spilled registers it took 32.4 us at 8 x 128 rows x 512
+// chunks, without 28.2.  (The other spills with a scalar wave number.)
 template <bool W8>
 __global__ __launch_bounds__(256, 4) void k_obs_chunks_once(ObsArgs a) {
   const int g = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = W8 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int T = a.T, n_rows = a.n_rows;
   const int lr = lane & 15, lq = lane >> 4;
   const int c = blockIdx.x * 4 + wave;           // this wave's chunk
@@ -357,23 +360,25 @@ __global__ __launch_bounds__(256, 4) void k_obs_chunks_once(ObsArgs a) {
       const float mu = mr > -INFINITY ? m : 0.f;    // all keys masked: every term is exp2(-inf) = 0
       float lA = 0.f, lB = 0.f;                     // keys of tiles 0-1 and 2-3
 #pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[kt][i] = __builtin_amdgcn_exp2f(fmaf(acc[kt][i], sc, -mu));
+#pragma unroll
       for (int i = 0; i < 4; ++i) {
-        lA += __builtin_amdgcn_exp2f(fmaf(acc[0][i], sc, -mu));
-        lA += __builtin_amdgcn_exp2f(fmaf(acc[1][i], sc, -mu));
-        lB += __builtin_amdgcn_exp2f(fmaf(acc[2][i], sc, -mu));
-        lB += __builtin_amdgcn_exp2f(fmaf(acc[3][i], sc, -mu));
+        lA += acc[0][i];
+        lA += acc[1][i];
+        lB += acc[2][i];
+        lB += acc[3][i];
       }
       if constexpr (W8) {
         // 8-token windows: tile kt holds windows 2 kt (lanes lq 0, 1) and 2 kt + 1
         // (lq 2, 3); the pair sums land in lanes lq 0 and 2
 #pragma unroll
         for (int kt = 0; kt < 4; ++kt) {
-          float lt = 0.f;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) lt += __builtin_amdgcn_exp2f(fmaf(acc[kt][i], sc, -mu));
+          float lt = ((acc[kt][0] + acc[kt][1]) + acc[kt][2]) + acc[kt][3];
           lt += __shfl_xor(lt, 16, 64);
-          const int w = w0 + 2 * kt + (lq >> 1);
-          if (row < nr && (lq & 1) == 0 && w >= 0 && w < a.n_w) wl_a[(int64_t)(w - w0) * n_rows + rg] = lt;
+          const int w = 2 * kt + (lq >> 1);          // of the chunk's eight
+          if (row < nr && (lq & 1) == 0 && w0 >= 0 && w0 + w < a.n_w) wl_a[w * n_rows + rg] = lt;
         }
       }
       lA = rows_sum(lA);
