@@ -377,7 +377,10 @@ hipError_t timed(qevict_cache* c, int kernel, hipStream_t st, F&& launch, int un
 // leaves free, and the queue-level wait, whose stall of the cache stream (about
 // 12 us a batch) gives it that room, was measured faster: 128K context with
 // 64-token windows (246-register attention), the RoPE-aware tier (256), GQA 8
-// (228 plus an 80-register migration wave).
+// (228 plus an 80-register migration wave).  Where it fits the gate is the faster one:
+// 8-token windows (179 / 191 / 210 registers by head sets, plus 53) take 23.7 us a step
+// against 25.5 with the queue-level wait (32K, GQA 4, 8 layer caches), 25.2 / 26.6 (16
+// caches), 98.3 / 99.2 (batch 8), 37.1 / 38.2 (GQA 8), 39.4 / 40.6 (GQA 16).
 hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
   int av = 0, mv = 0;
   size_t al = 0, ml = 0;
@@ -385,13 +388,7 @@ hipError_t routing_fits_beside_attention(const Geometry& g, bool* fits) {
   if (e == hipSuccess) e = migrate_footprint(g, &mv, &ml);
   if (e != hipSuccess) return e;
   auto granule = [](int v) { return (v + 7) / 8 * 8; };   // VGPR allocation granule
-  // Pairs of 8-token windows (at most four heads per KV head) fit too since their
-  // attention holds 179 registers, but callers see the queue-level wait reported for
-  // them and keep it; forced, the gate takes 24.4 against 25.3 us a step (4 layer
-  // caches, 32K), 25.2 / 26.1 (16).  With more heads the gate is both the order they
-  // had and the faster one: 37.1 / 38.2 us (GQA 8), 39.4 / 40.6 (GQA 16), 8 caches.
-  const bool pairs = g.W == 8 && g.gqa <= 4;
-  *fits = !pairs && 2 * granule(av) + granule(mv) <= 512 && 2 * al + ml <= 160 * 1024;
+  *fits = 2 * granule(av) + granule(mv) <= 512 && 2 * al + ml <= 160 * 1024;
   return hipSuccess;
 }
 

@@ -307,10 +307,11 @@ def test_async_routing_lockstep(name, kw, order):
         ls.close()
 
 
-@pytest.mark.parametrize("n_layers,twice,queue_wait", [(4, False, False), (9, False, False),
-                                                       (16, False, False), (5, True, False),
-                                                       (4, False, True), (9, False, True)])
-def test_async_routing_interleaved_layers_match_sync(n_layers, twice, queue_wait):
+@pytest.mark.parametrize("n_layers,twice,queue_wait,name", [(4, False, False, "c2s"), (9, False, False, "c2s"),
+                                                            (16, False, False, "c2s"), (5, True, False, "c2s"),
+                                                            (4, False, True, "c2s"), (9, False, True, "c2s"),
+                                                            (9, False, False, "c6w8s")])
+def test_async_routing_interleaved_layers_match_sync(n_layers, twice, queue_wait, name):
     """Several layers stepped back to back with no host synchronisation: the
     routing of each layer overlaps the attention of the others and every
     output and final state equals the single-stream run bit for bit.  Routing
@@ -323,7 +324,7 @@ def test_async_routing_interleaved_layers_match_sync(n_layers, twice, queue_wait
     import paper_2608_05326_amd as qv
     from tests.gpu_harness import gpu_config, to_dev_bf16
     torch = _torch()
-    wl = syn.get_workload("c2s")
+    wl = syn.get_workload(name)
     steps = 10
 
     def run(flags):
@@ -364,13 +365,14 @@ def test_async_routing_interleaved_layers_match_sync(n_layers, twice, queue_wait
 
 
 @pytest.mark.parametrize("name,kw,flags,order", [
-    ("c2s", {}, "async", "gate"),                     # 32-token windows, GQA 4: 204 + 204 + 79 registers
+    ("c2s", {}, "async", "gate"),                     # 32-token windows, GQA 4: 215 + 215 + 80 registers
     ("c6s", {}, "async", "gate"),
     ("c2s", {"rope_base": 500000.0}, "async", "queue"),   # RoPE-aware attention: 256 registers
-    ("c4s", {}, "async", "queue"),                    # 64-token windows: 256 registers
-    ("c5s", {}, "async", "queue"),                    # GQA 8: 217 + 217 + 79
-    ("c6w8s", {}, "async", "queue"),                  # 8-token windows: 222 + 222 + 96
+    ("c4s", {}, "async", "queue"),                    # 64-token windows: 246 registers
+    ("c5s", {}, "async", "queue"),                    # GQA 8: 228 + 228 + 80
+    ("c6w8s", {}, "async", "gate"),                   # 8-token windows: 179 + 179 + 53
     ("c2s", {}, "async+queue", "queue"),
+    ("c6w8s", {}, "async+queue", "queue"),
     ("c6w8s", {}, "async+device", "gate"),
     ("c2s", {}, "sync", "sync"),
 ])
