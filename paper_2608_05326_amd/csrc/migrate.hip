@@ -19,6 +19,8 @@
 // over its tokens with lane exchanges and form whole code words; value rows pass
 // through LDS, which turns the prompt's rows into the columns the chunks and code
 // words hold.
+#include <algorithm>
+
 #include "qv_device.h"
 
 namespace qv {
@@ -540,20 +542,25 @@ __device__ __forceinline__ void quantize_values(const Task& t, const WorkEntry& 
 
 // ---- promotions and admissions ---------------------------------------------
 
+// RNE_bf16 of a value whose fp32 rounding is f (off: f differs from it, above: it lies
+// above f): f is on the value's side of every bf16 tie unless f is that tie itself.
+__device__ __forceinline__ uint32_t bf16_of(float f, bool off, bool above) {
+  uint32_t u = __float_as_uint(f);
+  const bool tie = (u & 0xFFFFu) == 0x8000u && off;
+  u += tie ? (above == (f > 0.f) ? 1u : ~0u) : 0u;
+  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+
 // RNE_bf16(z + s c): s c is exact in fp32 (11-bit scale, 4-bit code); the sum is
-// rounded to fp32 with its error e (two-sum), which decides where the rounded sum
-// lies on a bf16 tie, so the result is that of one rounding of the exact value.
-// (Sums are multiples of 2^-24, so none is below the bf16 normal range.)
+// rounded to fp32 with its error e (two-sum), so the result is that of one rounding of
+// the exact value.  (Sums are multiples of 2^-24.)
 __device__ __forceinline__ uint32_t dequant_bf16(uint16_t zb, uint16_t sb, uint32_t code) {
   const float z = (float)__builtin_bit_cast(_Float16, zb), s = (float)__builtin_bit_cast(_Float16, sb);
   const float p = s * (float)code;
   const float f = z + p;
   const float pp = f - z;
   const float e = (z - (f - pp)) + (p - pp);
-  uint32_t u = __float_as_uint(f);
-  const bool tie = (u & 0xFFFFu) == 0x8000u && e != 0.f;
-  u += tie ? ((e > 0.f) == (f > 0.f) ? 1u : ~0u) : 0u;
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+  return bf16_of(f, e != 0.f, e > 0.f);
 }
 
 // 8 bf16 values z_j + s_j c_j (one rounding each) packed for a 16-byte store
@@ -615,46 +622,54 @@ __device__ __forceinline__ u32x4 rope_key8(const Geometry& G, const uint8_t* rec
       const float2 cs = rope_cs(G, p, (32 * kb + 8 * q + j) & 63);
       const double t1 = x[j] * (double)cs.x, t2 = y[j] * (double)cs.y;
       const double v = kb < 2 ? t1 - t2 : t1 + t2;
-      pair |= (uint32_t)f64_to_bf16_rne(v) << (16 * o);
+      const float f = (float)v;
+      pair |= bf16_of(f, (double)f != v, v > (double)f) << (16 * o);
     }
     outw[i] = pair;
   }
   return (u32x4){outw[0], outw[1], outw[2], outw[3]};
 }
 
-// Promotion of one part of a (window, KV head) from its quantized record: lane L
-// takes the code word, the 8 scales and the 8 zeros of each of its entries and
-// writes 8 bf16 values to the same (entry, lane) position of the bf16 slot.
+// Promotion of entry ei (of area's W / 4) of a (window, KV head) from its quantized
+// record: lane L takes its code word, 8 scales and 8 zeros and writes 8 bf16 values to
+// the same (entry, lane) position of the bf16 slot.
+template <int W, int NB, bool ROPE>
+__device__ __forceinline__ void promote_entry(const Geometry& G, const uint8_t* rec, uint8_t* dp, int area, int ei,
+                                              int L, int p0) {
+  constexpr int PER = 4 / NB;
+  if (ROPE && area == 0) {
+    *(u32x4*)(dp + ((int64_t)ei * 64 + L) * 16) = rope_key8<NB>(G, rec, ei, L, p0);
+    return;
+  }
+  const int ng = kHeadDim / G.G;
+  const int q = L >> 4, r = L & 15;
+  const int word = ei / PER;
+  const uint32_t wd = *(const uint32_t*)(rec + area * G.qcodes_bytes +
+                                         ((int64_t)(word >> 2) * 64 + L) * 16 + (word & 3) * 4);
+  const uint8_t* ps;
+  u32x4 s8, z8;
+  if (area == 0) {   // key entry (tb, kb): channels 32 kb + 8 q .. + 7
+    ps = rec + meta_k_off(G) + 2 * (32 * (ei & 3) + 8 * q);
+    s8 = *(const u32x4*)ps;
+    z8 = *(const u32x4*)(ps + 2 * kHeadDim);
+  } else {           // value entry (kt, cb): tokens tok(kt, q, 0..7), channel 16 cb + r
+    const int c = 16 * (ei & 7) + r;
+    ps = rec + meta_v_off(G) + (((ei >> 3) * 4 + q) * ng + c / G.G) * 32;
+    s8 = *(const u32x4*)ps;
+    z8 = *(const u32x4*)(ps + 16);
+  }
+  const int64_t off = (area == 0 ? 0 : (int64_t)W * kHeadDim * 2) + ((int64_t)ei * 64 + L) * 16;
+  *(u32x4*)(dp + off) = dequant8<NB>(wd, ei % PER, s8, z8);
+}
+
+// Promotion of one part of a (window, KV head).
 template <int W, int NB, bool ROPE>
 __device__ __forceinline__ void promote_record(const Geometry& G, const uint8_t* rec, uint8_t* dp, int area, int h,
                                                int L, int p0) {
-  constexpr int PER = 4 / NB;
-  const int ng = kHeadDim / G.G;
-  const int q = L >> 4, r = L & 15;
 #pragma unroll 4   // the loads of four entries in one round
   for (int o = 0; o < W / 8; ++o) {
     const int ei = area == 0 ? 4 * (o >> 1) + key_block<ROPE>(h, o & 1) : 8 * (o >> 2) + 4 * h + (o & 3);
-    if (ROPE && area == 0) {
-      *(u32x4*)(dp + ((int64_t)ei * 64 + L) * 16) = rope_key8<NB>(G, rec, ei, L, p0);
-      continue;
-    }
-    const int word = ei / PER;
-    const uint32_t wd = *(const uint32_t*)(rec + area * G.qcodes_bytes +
-                                           ((int64_t)(word >> 2) * 64 + L) * 16 + (word & 3) * 4);
-    const uint8_t* ps;
-    u32x4 s8, z8;
-    if (area == 0) {   // key entry (tb, kb): channels 32 kb + 8 q .. + 7
-      ps = rec + meta_k_off(G) + 2 * (32 * (ei & 3) + 8 * q);
-      s8 = *(const u32x4*)ps;
-      z8 = *(const u32x4*)(ps + 2 * kHeadDim);
-    } else {           // value entry (kt, cb): tokens tok(kt, q, 0..7), channel 16 cb + r
-      const int c = 16 * (ei & 7) + r;
-      ps = rec + meta_v_off(G) + (((ei >> 3) * 4 + q) * ng + c / G.G) * 32;
-      s8 = *(const u32x4*)ps;
-      z8 = *(const u32x4*)(ps + 16);
-    }
-    const int64_t off = (area == 0 ? 0 : (int64_t)W * kHeadDim * 2) + ((int64_t)ei * 64 + L) * 16;
-    *(u32x4*)(dp + off) = dequant8<NB>(wd, ei % PER, s8, z8);
+    promote_entry<W, NB, ROPE>(G, rec, dp, area, ei, L, p0);
   }
 }
 
@@ -746,8 +761,8 @@ __device__ __forceinline__ void promote_part(const Task& t, const WorkEntry& ent
 // Bound by memory for a prompt and by the latency of one task for a routing event.
 // Admission of a 32K prompt (8 KV heads, 204 windows copied, 307 quantized to int4;
 // 106 MB moved): 78.7 -> 24.8 us; four 64K prompts (964 MB): 582 -> 192 us, 5.0 TB/s,
-// against one looping workgroup per part with every code decided in float64.  An
-// event that moves a window or two: 6.4 -> 6.9 us (one wave does what four did).
+// against one looping workgroup per part with every code decided in float64.  (Events of
+// few windows, where one wave would do what four did: k_migrate_few.)
 // At most 80 VGPRs without RoPE and with windows of 8 or 32 tokens (six waves per
 // SIMD): a migration workgroup then fits on a compute unit beside two attention
 // workgroups of up to 216, so routing on its own stream does not hold back the
@@ -797,6 +812,241 @@ __global__ __launch_bounds__(kMigrateThreads, (migrate_waves_per_simd<W, ROPE>()
   }
 }
 
+// ---- routing events of a few windows ---------------------------------------
+// The same migrations with half a part per wave (32- and 64-token windows, no prompt
+// source): a workgroup takes the keys or the values of one (window, KV head), wave
+// (h, sub) of it the key block key_block(h, sub), or of channel half h the values of
+// value group sub (32-token windows) or of token block sub (64).
+// Bound by latency: one task's chain of loads, reductions and codes (a task of
+// k_migrate's waves is twice as long), and the float64 rotation with RoPE.  One layer's
+// event after a decode step, 8 KV heads, 5 to 6 promotions and as many windows quantized
+// at first, medians: 10.4 -> 5.2 us (32K, int4), 9.8 -> 5.8 (128K, 64-token windows),
+// 22.9 -> 6.6 with RoPE; with four workgroups per (window, KV head) whose waves shared a
+// part in barrier-separated phases 7.9, 7.1 and 15.8.
+template <int W>
+constexpr int few_channels() { return W == 32 ? 32 : 64; }   // of a wave's value rows (32 tokens)
+template <int W>
+constexpr int few_row() { return few_channels<W>() + 8; }
+template <int W>
+struct FewLds {    // of one wave
+  uint16_t rows[32 * few_row<W>()];
+  GroupParams gp[32];   // keys: channel of the block; values: token
+};
+
+template <int W, bool ROPE>
+__device__ __forceinline__ void quantize_key_block(const Task& t, const WorkEntry& ent, GroupParams* gp,
+                                                   int32_t* counts, int h, int sub, int lane) {
+  const Geometry& G = t.a.g;
+  constexpr int TB = W / 16;
+  const int w = ent.v[0], nb = ent.v[4], kb = key_block<ROPE>(h, sub);
+  const uint8_t* src = t.slot(ent.v[1], ent.v[2]);
+  u32x4 x[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) x[tb] = gld16(src + ((tb * 4 + kb) * 64 + lane) * 16);
+  if constexpr (ROPE) {   // as unrotate_keys, for this block's channels of the pairs
+#pragma clang fp contract(off)
+    const int pb = key_block<ROPE>(h, 1 - sub), i0 = 32 * h + 8 * (lane >> 4);
+    u32x4 y[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) y[tb] = gld16(src + ((tb * 4 + pb) * 64 + lane) * 16);
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      const int p = G.sink + w * W + 16 * tb + (lane & 15);
+      u32x4 z = x[tb];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        uint32_t zw = 0;
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          const float2 cs = rope_cs(G, p, i0 + 2 * d + o);
+          const float c = elem_f32(x[tb], 2 * d + o) * cs.x, s = elem_f32(y[tb], 2 * d + o) * cs.y;
+          zw |= (uint32_t)f32_to_bf16_rne(sub ? c - s : c + s) << (16 * o);
+        }
+        z[d] = zw;
+      }
+      x[tb] = z;
+    }
+  }
+  // extremes of the block's channels: lanes 2 c, 2 c + 1 of a row end with channel c
+  float mn[8], mx[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) mn[j] = mx[j] = elem_f32(x[0], j);
+#pragma unroll
+  for (int tb = 1; tb < TB; ++tb)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float v = elem_f32(x[tb], j);
+      mn[j] = fminf(mn[j], v);
+      mx[j] = fmaxf(mx[j], v);
+    }
+  scatter_minmax<4, kXor8>(mn, mx, (lane & 8) != 0);
+  scatter_minmax<2, kXor7>(mn, mx, (lane & 4) != 0);
+  scatter_minmax<1, kXor2>(mn, mx, (lane & 2) != 0);
+  const float lo = fminf(mn[0], dpp<kXor1>(mn[0])), hi = fmaxf(mx[0], dpp<kXor1>(mx[0]));
+  uint8_t* rec = t.record(ent.v[3]);
+  if ((lane & 1) == 0) {
+    const int c = lane >> 1;   // channel of the block: 8 (lane >> 4) + (lane & 15) / 2
+    uint16_t zb, sb;
+    group_params(lo, hi, nb, &gp[c], &zb, &sb, counts);
+    uint16_t* mk = (uint16_t*)(rec + meta_k_off(G)) + 32 * kb + c;
+    mk[0] = sb;
+    mk[kHeadDim] = zb;
+  }
+  lds_order();
+  GroupParams p[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) p[j] = gp[8 * (lane >> 4) + j];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const uint32_t wd =
+        entry_codes(nb, [&](int j) { return elem_f32(x[tb], j); }, [&](int j) { return p[j]; });
+    if (nb == 4) {
+      *(uint32_t*)(rec + (tb * 64 + lane) * 16 + 4 * kb) = wd;
+    } else {   // entry kb & 1 of word 2 tb + kb / 2: its bytes kb & 1 and + 2
+      uint8_t* d = rec + ((tb >> 1) * 64 + lane) * 16 + (2 * (tb & 1) + (kb >> 1)) * 4 + (kb & 1);
+      d[0] = (uint8_t)wd;
+      d[2] = (uint8_t)(wd >> 16);
+    }
+  }
+}
+
+template <int W>
+__device__ __forceinline__ void quantize_value_block(const Task& t, const WorkEntry& ent, FewLds<W>& sm,
+                                                     int32_t* counts, int h, int sub, int lane) {
+  const Geometry& G = t.a.g;
+  constexpr int NC = W == 32 ? 2 : 4;              // 16-channel blocks
+  constexpr int RS = few_row<W>();
+  constexpr int CL = few_channels<W>() / 2;        // channels a lane reduces
+  const int nb = ent.v[4], r = lane & 15, q = lane >> 4;
+  const int kt = W == 32 ? 0 : sub, cl0 = W == 32 ? 2 * sub : 0;   // token block, first block of the half
+  const uint8_t* src = t.slot(ent.v[1], ent.v[2]) + (int64_t)W * kHeadDim * 2;
+  u32x4 x[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) x[c] = gld16(src + ((kt * 8 + 4 * h + cl0 + c) * 64 + lane) * 16);
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      sm.rows[v_tok(0, q, j) * RS + 16 * c + r] = (uint16_t)(x[c][j >> 1] >> (16 * (j & 1)));
+  lds_order();
+  uint8_t* rec = t.record(ent.v[3]);
+  {   // extremes of token lane / 2: half its channels in the lane, then the two halves
+    float mn = 0.f, mx = 0.f;
+#pragma unroll
+    for (int k = 0; k < CL / 8; ++k) {
+      const u32x4 v = *(const u32x4*)(sm.rows + (lane >> 1) * RS + CL * (lane & 1) + 8 * k);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float f = elem_f32(v, j);
+        mn = k + j == 0 ? f : fminf(mn, f);
+        mx = k + j == 0 ? f : fmaxf(mx, f);
+      }
+    }
+    mn = fminf(mn, dpp<kXor1>(mn));
+    mx = fmaxf(mx, dpp<kXor1>(mx));
+    if ((lane & 1) == 0) {
+      uint16_t zb, sb;
+      group_params(mn, mx, nb, &sm.gp[lane >> 1], &zb, &sb, counts);
+      uint8_t* mv = rec + meta_v_elem(G, 32 * kt + (lane >> 1), W == 32 ? 2 * h + sub : h);
+      *(uint16_t*)mv = sb;
+      *(uint16_t*)(mv + meta_v_zero_delta(G)) = zb;
+    }
+  }
+  lds_order();
+  GroupParams p[8];   // of the lane's 8 tokens tok(kt, q, j): two runs of four
+#pragma unroll
+  for (int j = 0; j < 8; ++j) p[j] = sm.gp[v_tok(0, q, j)];
+  uint32_t wds[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    wds[c] = entry_codes(
+        nb, [&](int j) { return elem_f32(x[c], j); }, [&](int j) { return p[j]; });
+  uint8_t* vc = rec + G.qcodes_bytes;
+  if constexpr (W == 32) {
+    if (nb == 4) *(uint2*)(vc + (h * 64 + lane) * 16 + 8 * sub) = make_uint2(wds[0], wds[1]);
+    else *(uint32_t*)(vc + lane * 16 + 8 * h + 4 * sub) = wds[0] | (wds[1] << 8);
+  } else {
+    if (nb == 4)
+      *(u32x4*)(vc + ((2 * kt + h) * 64 + lane) * 16) = (u32x4){wds[0], wds[1], wds[2], wds[3]};
+    else
+      *(uint2*)(vc + (kt * 64 + lane) * 16 + 8 * h) = make_uint2(wds[0] | (wds[1] << 8), wds[2] | (wds[3] << 8));
+  }
+  lds_order();   // the rows are read before a task that follows stages its own
+}
+
+template <int W, bool ROPE>
+__device__ __forceinline__ void promote_half_part(const Task& t, const WorkEntry& ent, int area, int h, int sub,
+                                                  int lane) {
+  const Geometry& G = t.a.g;
+  const int w = ent.v[0], src_kind = ent.v[1], src_idx = ent.v[2], nb = ent.v[4];
+  uint8_t* dp = t.slot(SRC_FSLOT, ent.v[3]);
+  constexpr int NE = W / 16;   // entries (chunks) of half a part
+  auto entry = [&](int o) {
+    return area == 0 ? 4 * o + key_block<ROPE>(h, sub) : W == 32 ? 4 * h + 2 * sub + o : 8 * sub + 4 * h + o;
+  };
+  if (src_kind == SRC_QSLOT) {
+    const uint8_t* rec = t.record(src_idx);
+    const int p0 = G.sink + w * W;   // position of the window's first token
+#pragma unroll
+    for (int o = 0; o < NE; ++o) {
+      if (nb == 4) promote_entry<W, 4, ROPE>(G, rec, dp, area, entry(o), lane, p0);
+      else promote_entry<W, 2, ROPE>(G, rec, dp, area, entry(o), lane, p0);
+    }
+  } else {
+    const uint8_t* sp = t.slot(SRC_RING, src_idx);
+    const int64_t base = area == 0 ? 0 : (int64_t)W * kHeadDim * 2;
+    u32x4 x[NE];
+#pragma unroll
+    for (int o = 0; o < NE; ++o) x[o] = gld16(sp + base + ((int64_t)entry(o) * 64 + lane) * 16);
+#pragma unroll
+    for (int o = 0; o < NE; ++o) *(u32x4*)(dp + base + ((int64_t)entry(o) * 64 + lane) * 16) = x[o];
+  }
+}
+
+template <int W, bool ROPE>
+__global__ __launch_bounds__(kMigrateThreads, (migrate_waves_per_simd<W, ROPE>())) void k_migrate_few(MigrateArgs a) {
+  const Geometry& G = a.g;
+  const int b = blockIdx.y + touch_kernargs<sizeof(MigrateArgs)>();
+  __shared__ __attribute__((aligned(16))) FewLds<W> sm[4];
+  uint8_t* ub = a.base[blockIdx.z] + (int64_t)b * a.L.unit_bytes;   // (the rounds of loads: as k_migrate)
+  int32_t* counts = (int32_t*)(ub + a.L.counts);
+  const int32_t* plist = (const int32_t*)(ub + a.L.plist);
+  const bool quant = (int)blockIdx.x < a.n_quant_blocks;
+  const int stride = quant ? a.n_quant_blocks : a.n_promote_blocks;
+  const int x0 = quant ? blockIdx.x : blockIdx.x - a.n_quant_blocks;
+  const int32_t* list = (const int32_t*)(ub + (quant ? a.L.qlist : a.L.plist));
+  const int32_t* gate = a.gate_fail ? a.gate_fail : counts;
+  const int per = 2 * G.H_kv;   // tasks of an entry
+  const int e0 = x0 / per;
+  const int n_entries = counts[quant ? CNT_QUANT : CNT_PROMOTE];
+  const WorkEntry first = load_entry(list, e0 <= G.max_fq ? e0 : 0);
+  const int gate_word = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int n_tasks = a.gate_fail && gate_word ? 0 : n_entries * per;
+  int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = wave >> 1, sub = wave & 1;
+  for (int task = x0; task < n_tasks; task += stride) {
+    asm volatile("" : "+v"(lane));   // (as in k_migrate)
+    const WorkEntry ent = task == x0 ? first : load_entry(list, task / per);
+    const int rest = task % per, area = rest / G.H_kv;
+    const Task t{a, ub, b, rest - area * G.H_kv};
+    WorkEntry pe = ent;
+    bool promote = !quant && ent.v[5] < 0;
+    if (quant) {
+      if (area == 0) quantize_key_block<W, ROPE>(t, ent, sm[wave].gp, counts, h, sub, lane);
+      else quantize_value_block<W>(t, ent, sm[wave], counts, h, sub, lane);
+      promote = ent.v[5] >= 0;
+      if (promote) {
+        pe = load_entry(plist, ent.v[5]);
+        // with RoPE a wave also read the block that its partner overwrites (the task is
+        // the workgroup's: all four waves come here)
+        if constexpr (ROPE) __syncthreads();
+      }
+    }
+    if (promote) promote_half_part<W, ROPE>(t, pe, area, h, sub, lane);
+  }
+}
+
 // Copy the prompt's sink tokens [0, n_sink) and its tail [tail0, src_T) into the
 // sink slots and the recent ring: one thread per (token, 8 channels, keys or
 // values), 8 tokens a workgroup, so that a copy is one round of loads.
@@ -823,6 +1073,14 @@ __global__ __launch_bounds__(256) void k_pack_tokens(PackArgs a) {
   }
 }
 
+// The form with half a part per wave: two workgroups per (window, KV head) of the event's
+// windows or of eight, which most events after a single step stay below (with four, the
+// mean event below took 7.0 instead of 5.5 us), as long as that is a wave of workgroups
+// on the chip (six a compute unit) and some.  Larger launches are mostly idle workgroups,
+// whose number then counts, and take the form with fewer.
+constexpr int kFewBlocks = 2048, kFewWindows = 8;
+static int few_blocks(const Geometry& g, int entries) { return 2 * g.H_kv * std::max(entries, kFewWindows); }
+
 // Workgroups for `entries` windows: one per (window, KV head), at most 16384
 // (larger events loop).  A prompt's migrations (2456 quantizations and 1632
 // admissions at 32K with 8 KV heads) then run without a serial chain of tasks in
@@ -833,32 +1091,51 @@ static int migrate_blocks(const Geometry& g, int entries) {
 }
 
 hipError_t launch_migrate(MigrateArgs a, int max_quant, int max_promote, hipStream_t st) {
-  a.n_quant_blocks = migrate_blocks(a.g, max_quant);
-  a.n_promote_blocks = migrate_blocks(a.g, max_promote);
-  const dim3 grid(a.n_quant_blocks + a.n_promote_blocks, a.g.B, a.n_units);
-  if (a.g.rope) {
-    if (a.g.W == 32) hipLaunchKernelGGL((k_migrate<32, true>), grid, dim3(kMigrateThreads), 0, st, a);
+  const Geometry& g = a.g;
+  const int fq = few_blocks(g, max_quant), fp = few_blocks(g, max_promote);
+  if (!a.src_k && g.W != 8 && (int64_t)(fq + fp) * g.B * a.n_units <= kFewBlocks) {
+    a.n_quant_blocks = fq;
+    a.n_promote_blocks = fp;
+    const dim3 grid(fq + fp, g.B, a.n_units);
+    if (g.rope && g.W == 32) hipLaunchKernelGGL((k_migrate_few<32, true>), grid, dim3(kMigrateThreads), 0, st, a);
+    else if (g.rope) hipLaunchKernelGGL((k_migrate_few<64, true>), grid, dim3(kMigrateThreads), 0, st, a);
+    else if (g.W == 32) hipLaunchKernelGGL((k_migrate_few<32, false>), grid, dim3(kMigrateThreads), 0, st, a);
+    else hipLaunchKernelGGL((k_migrate_few<64, false>), grid, dim3(kMigrateThreads), 0, st, a);
+    return hipGetLastError();
+  }
+  a.n_quant_blocks = migrate_blocks(g, max_quant);
+  a.n_promote_blocks = migrate_blocks(g, max_promote);
+  const dim3 grid(a.n_quant_blocks + a.n_promote_blocks, g.B, a.n_units);
+  if (g.rope) {
+    if (g.W == 32) hipLaunchKernelGGL((k_migrate<32, true>), grid, dim3(kMigrateThreads), 0, st, a);
     else hipLaunchKernelGGL((k_migrate<64, true>), grid, dim3(kMigrateThreads), 0, st, a);
   } else {
-    if (a.g.W == 8) hipLaunchKernelGGL((k_migrate<8, false>), grid, dim3(kMigrateThreads), 0, st, a);
-    else if (a.g.W == 32) hipLaunchKernelGGL((k_migrate<32, false>), grid, dim3(kMigrateThreads), 0, st, a);
+    if (g.W == 8) hipLaunchKernelGGL((k_migrate<8, false>), grid, dim3(kMigrateThreads), 0, st, a);
+    else if (g.W == 32) hipLaunchKernelGGL((k_migrate<32, false>), grid, dim3(kMigrateThreads), 0, st, a);
     else hipLaunchKernelGGL((k_migrate<64, false>), grid, dim3(kMigrateThreads), 0, st, a);
   }
   return hipGetLastError();
 }
-// Registers per lane and LDS bytes per workgroup of the migration kernel a
-// geometry launches.
+// Registers per lane and LDS bytes per workgroup of the migration kernels a geometry
+// launches (the larger of its forms).
 hipError_t migrate_footprint(const Geometry& g, int* vgprs, size_t* lds) {
-  const void* k = g.rope ? (g.W == 32 ? reinterpret_cast<const void*>(&k_migrate<32, true>)
-                                      : reinterpret_cast<const void*>(&k_migrate<64, true>))
-                 : g.W == 8  ? reinterpret_cast<const void*>(&k_migrate<8, false>)
-                 : g.W == 32 ? reinterpret_cast<const void*>(&k_migrate<32, false>)
-                             : reinterpret_cast<const void*>(&k_migrate<64, false>);
-  hipFuncAttributes fa;
-  hipError_t e = hipFuncGetAttributes(&fa, k);
-  if (e != hipSuccess) return e;
-  *vgprs = fa.numRegs;
-  *lds = fa.sharedSizeBytes;
+  auto ptr = [](auto* k) { return reinterpret_cast<const void*>(k); };
+  const void* ks[2] = {nullptr, nullptr};
+  if (g.W == 8) ks[0] = ptr(&k_migrate<8, false>);
+  else if (g.W == 32 && g.rope) ks[0] = ptr(&k_migrate<32, true>), ks[1] = ptr(&k_migrate_few<32, true>);
+  else if (g.W == 32) ks[0] = ptr(&k_migrate<32, false>), ks[1] = ptr(&k_migrate_few<32, false>);
+  else if (g.rope) ks[0] = ptr(&k_migrate<64, true>), ks[1] = ptr(&k_migrate_few<64, true>);
+  else ks[0] = ptr(&k_migrate<64, false>), ks[1] = ptr(&k_migrate_few<64, false>);
+  *vgprs = 0;
+  *lds = 0;
+  for (const void* k : ks) {
+    if (!k) continue;
+    hipFuncAttributes fa;
+    hipError_t e = hipFuncGetAttributes(&fa, k);
+    if (e != hipSuccess) return e;
+    *vgprs = std::max(*vgprs, fa.numRegs);
+    *lds = std::max(*lds, (size_t)fa.sharedSizeBytes);
+  }
   return hipSuccess;
 }
 hipError_t launch_pack_tokens(const PackArgs& a, hipStream_t st) {

@@ -184,26 +184,6 @@ __device__ inline uint16_t fp16_round_down(float x) {
   return h;
 }
 
-// exact float64 -> bf16, round to nearest even, single rounding
-__device__ inline uint16_t f64_to_bf16_rne(double x) {
-  uint64_t u = __double_as_longlong(x);
-  uint16_t sign = (uint16_t)((u >> 48) & 0x8000u);
-  uint64_t a = u & 0x7FFFFFFFFFFFFFFFull;
-  if (a == 0) return sign;
-  int e = (int)(a >> 52) - 1023;
-  if (e >= -126) {
-    uint64_t mant = a & ((1ull << 52) - 1);
-    uint64_t m7 = mant >> 45, rem = mant & ((1ull << 45) - 1), half = 1ull << 44;
-    if (rem > half || (rem == half && (m7 & 1))) m7 += 1;
-    if (m7 == 128) { m7 = 0; e += 1; }
-    if (e > 127) return (uint16_t)(sign | 0x7F80u);
-    return (uint16_t)(sign | ((uint32_t)(e + 127) << 7) | (uint32_t)m7);
-  }
-  // below the bf16 normal range: integer multiple of 2^-133
-  double y = __builtin_rint(__builtin_fabs(x) * 0x1p133);
-  return (uint16_t)(sign | (uint16_t)y);
-}
-
 __device__ inline void set_error(int32_t* counts, int32_t bits) {
   __hip_atomic_fetch_or(counts + CNT_ERROR, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

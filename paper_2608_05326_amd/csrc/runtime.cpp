@@ -968,8 +968,8 @@ qevict_status qevict_retier(qevict_cache* c, int32_t layer, qevict_retier_stats*
   unit.aged_w0 = a0;
   unit.aged_w1 = a1 > a0 ? a1 : a0;
   plan_next(g, c->cfg.max_context, ls.T + 1, c->cfg.retier_interval, unit.aged_w1, &unit);
-  // grid of the migration launch: sized for the windows a routing event usually
-  // moves (a few per step between events); larger events loop inside the kernel
+  // windows the migration launch is sized for: those a routing event usually moves (a
+  // few per step between events); larger events loop inside the kernel
   const int max_q = std::min(std::max(g.K_q, g.K_f), 4 * c->cfg.retier_interval);
   hipError_t e = hipSuccess;
   if (c->rstream) {
