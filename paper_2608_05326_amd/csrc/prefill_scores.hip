@@ -189,11 +189,14 @@ __device__ __forceinline__ void obs_chunk(const ObsArgs& a, const u32x4 (&kop)[2
 // 8 x 512 rows x 2048 chunks (128K; 268 MB of keys, 137 GFLOP), 226 -> 184 us at
 // 32 x 256 rows x 1024 chunks (four 64K prompts, 537 MB), 40.6 -> 38.6 us at 8 x 128
 // rows x 1024 chunks (64K).
-// The chunks of all (sequence, KV head) pairs are one list of which every workgroup
-// takes an equal contiguous part (staging the next pair's rows where it crosses one):
-// a whole number of workgroups per pair left compute units without work (136 pairs
-// on 256) or ran a second, nearly empty wave of workgroups (264).  Parts of whole
-// rounds of eight chunks are not equal enough: 78 -> 82 us at 8 pairs x 625 chunks.
+// Where whole workgroups per (sequence, KV head) pair fill the chip, a pair's chunks go
+// round its `share` workgroups (their reads then follow one another through the keys;
+// parts of 1 MB each, a power of two apart, took 2% longer).  Otherwise (share 0) the
+// chunks of all pairs are one list of which every workgroup takes an equal contiguous
+// part, staging the next pair's rows where it crosses one: whole workgroups left compute
+// units without work (136 pairs on 256) or ran a second, nearly empty wave of workgroups
+// (264).  Parts of whole rounds of eight chunks are not equal enough: 78 -> 82 us at 8
+// pairs x 625 chunks.
 // 32x32 tiles halve the cross-lane work of 16x16 ones: a row's 64 logits lie in two
 // lanes instead of four, one lane exchange serves both window sums, and a tile's
 // masks, addresses and stores serve 32 rows.
@@ -206,18 +209,22 @@ __device__ __forceinline__ void obs_chunk(const ObsArgs& a, const u32x4 (&kop)[2
 constexpr int kObsWaves = kObsThreads / 64;
 constexpr int kObsUnits = 256;         // compute units (and resident workgroups)
 template <bool W8>
-__global__ __launch_bounds__(kObsThreads, 1) void k_obs_chunks(ObsArgs a) {
+__global__ __launch_bounds__(kObsThreads, 1) void k_obs_chunks(ObsArgs a, int share) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   __shared__ __attribute__((aligned(16))) uint8_t sq[kObsRows * kObsRowBytes];
-  const int64_t total = (int64_t)a.n_chunks * a.B * a.H_kv;   // (2^31 chunks of keys exceed any memory)
-  const int begin = (int)(total * blockIdx.x / gridDim.x), end = (int)(total * (blockIdx.x + 1) / gridDim.x);
+  // this workgroup's part [begin, end) of all pairs' chunks (2^31 chunks of keys exceed
+  // any memory); with a share, the whole pair, of which it takes every share-th chunk
+  const int64_t total = (int64_t)a.n_chunks * a.B * a.H_kv;
+  const int parts = share ? gridDim.x / share : gridDim.x, part = share ? blockIdx.x / share : blockIdx.x;
+  const int begin = (int)(total * part / parts), end = (int)(total * (part + 1) / parts);
+  const int step = kObsWaves * max(share, 1);
   for (int at = begin; at < end;) {
     const int pair = __builtin_amdgcn_readfirstlane(at / a.n_chunks);
     const int64_t bg = pair;
-    // the pair's chunks [c0, c_end) of this part; the wave after the one that took the
+    // the pair's chunks [c0, c_end) of the part; the wave after the one that took the
     // part's last chunk so far takes the first
     const int c0 = at - pair * a.n_chunks, c_end = min(c0 + end - at, a.n_chunks);
-    const int c_first = c0 + ((wave - (at - begin)) & (kObsWaves - 1));
+    const int c_first = share ? wave * share + (int)blockIdx.x % share : c0 + ((wave - (at - begin)) & (kObsWaves - 1));
     at += c_end - c0;
     const uint16_t* kb = a.k + bg * a.T * kHeadDim;
     const uint16_t* qb = a.q + bg * a.gqa * a.n_obs * kHeadDim;   // (H_q = H_kv * gqa)
@@ -245,8 +252,8 @@ __global__ __launch_bounds__(kObsThreads, 1) void k_obs_chunks(ObsArgs a) {
         *(u32x4*)(sq + row * kObsRowBytes + 16 * part) = x;
       }
       __syncthreads();
-      for (; c < c_end; c += 2 * kObsWaves) {
-        const int c1 = c + kObsWaves, c2 = c1 + kObsWaves;
+      for (; c < c_end; c += 2 * step) {
+        const int c1 = c + step, c2 = c1 + step;
         if (c1 < c_end) load(c1, k1);
         obs_chunk<W8>(a, k0, sq, c, bg, r0, nr, lane);
         if (c1 < c_end) {
@@ -506,12 +513,14 @@ hipError_t launch_prefill_scores(const ObsArgs& a, hipStream_t st) {
     if (a.W == 8) hipLaunchKernelGGL(k_obs_chunks_once<true>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(k_obs_chunks_once<false>, grid, dim3(256), 0, st, a);
   } else {   // (more than 4096 chunks: two or more a wave)
-    // A whole number of workgroups per pair where they fill 15 of 16 units (none then
-    // crosses from pair to pair: 92 -> 87 us at 12 pairs x 384 rows x 625 chunks).
-    const int64_t pairs = (int64_t)a.H_kv * a.B, whole = kObsUnits / pairs * pairs;
-    const dim3 grid((unsigned)(16 * whole >= 15 * kObsUnits ? whole : kObsUnits));
-    if (a.W == 8) hipLaunchKernelGGL(k_obs_chunks<true>, grid, dim3(kObsThreads), 0, st, a);
-    else hipLaunchKernelGGL(k_obs_chunks<false>, grid, dim3(kObsThreads), 0, st, a);
+    // whole workgroups per pair where they fill 15 of 16 units (12 pairs x 384 rows x 625
+    // chunks: 87 against 92 us with equal parts)
+    const int64_t pairs = (int64_t)a.H_kv * a.B;
+    int share = (int)(kObsUnits / pairs);
+    if (16 * share * pairs < 15 * kObsUnits) share = 0;
+    const dim3 grid((unsigned)(share ? share * pairs : kObsUnits));
+    if (a.W == 8) hipLaunchKernelGGL(k_obs_chunks<true>, grid, dim3(kObsThreads), 0, st, a, share);
+    else hipLaunchKernelGGL(k_obs_chunks<false>, grid, dim3(kObsThreads), 0, st, a, share);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
