@@ -363,7 +363,7 @@ __device__ __forceinline__ void dma16(const void* g, uint8_t* lds_row) {
 // Starts the loads of an item's record into its slot: a bf16 window (keys then
 // values) is four full rows of 1 KiB, a quantized record (key codes, value codes, key
 // scale / zero, value scale / zero) one full row and part of a second (at most 1664
-// bytes, at least 1056).
+// bytes, at least 1152).
 __device__ __forceinline__ void issue_record(const ItemInfo& in, uint8_t* dst, int lane, const Geometry& G) {
   const uint8_t* p = in.p + lane * 16;
   dma16(p, dst);

@@ -7,9 +7,10 @@
 //   z = largest fp16 <= min(x); s = smallest fp16 >= 0 with z + n s >= max(x);
 //   c = round-half-even((x - z) / s)   (all codes 0 when s = 0).
 // z + k s / 2 is exact in float64 for the integers k involved (fp16 operands),
-// so every comparison that decides s or a code is exact and the result is
-// bit-identical to the definition.  Keys form one group per channel across the
-// window's tokens, values one group per token across G channels.
+// so the comparisons that decide s are exact; a code comes from an fp32 quotient
+// where that decides as the exact one (see entry_codes) and from those boundaries
+// elsewhere.  The result is bit-identical to the definition.  Keys form one group per
+// channel across the window's tokens, values one group per token across G channels.
 // Promotion writes RNE_bf16(z + s c), one rounding of the exact value.
 //
 // One wave takes one part of one (window, KV head): the keys or the values of one
@@ -18,7 +19,7 @@
 // slots straight into registers (also from the prompt's rows), reduce each channel
 // over its tokens with lane exchanges and form whole code words; value rows pass
 // through LDS, which turns the prompt's rows into the columns the chunks and code
-// words hold.
+// words hold.  Routing events of few windows take half a part per wave (k_migrate_few).
 #include <algorithm>
 
 #include "qv_device.h"

@@ -271,12 +271,13 @@ __device__ __forceinline__ f32x4 mfma_obs16(bf16x8 a, bf16x8 b, f32x4 c) {
 }
 
 // The same for prompts whose chunks all fit the chip at once (at most 16 waves a
-// compute unit) and for few rows: one chunk per wave, four to a workgroup, logits by
-// 16x16x32 MFMAs.  With nothing to overlap across chunks, or little to compute for
-// one, more and shorter waves hide more latency: 25.7 against 29.1 us at 8 x 128 rows x
-// 512 chunks (32K), 6.2 against 7.4 at 8 x 32 rows x 33 chunks (2K), 42.7 against 45.0
-// (all three launches) at 8 x 32 rows x 1024 chunks (64K).
-// four workgroups per compute unit (at most 128 VGPRs); W8: 8-token windows (eight
+// compute unit), for few rows and for prompts of at most eight chunks: one chunk per
+// wave, four to a workgroup, logits by 16x16x32 MFMAs.  With nothing to overlap across
+// chunks, or little to compute for one, more and shorter waves hide more latency: 25.7
+// against 29.1 us at 8 x 128 rows x 512 chunks (32K), 6.2 against 7.4 at 8 x 32 rows x
+// 33 chunks (2K); all three launches 42.7 against 45.0 at 8 x 32 rows x 1024 chunks
+// (64K), 53.6 against 57.3 at 1024 x 128 rows x 6 chunks.
+// Four workgroups per compute unit (at most 128 VGPRs); W8: 8-token windows (eight
 // per chunk), a separate instantiation so the other window sizes carry none of it.
 // That one holds its chunk's addresses in scalar registers (a scalar wave number) and
 // each exponential once: with 9 spilled registers it took 32.4 us at 8 x 128 rows x 512
