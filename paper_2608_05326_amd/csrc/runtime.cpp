@@ -35,7 +35,7 @@ hipError_t attend_footprint(const Geometry& g, int* vgprs, size_t* lds);
 hipError_t migrate_footprint(const Geometry& g, int* vgprs, size_t* lds);
 hipError_t launch_gate_wait(const uint64_t* seq, uint64_t value, int32_t* fail, int64_t ticks,
                             hipStream_t st);
-hipError_t launch_migrate(MigrateArgs a, int max_quant, int max_promote, hipStream_t st);
+hipError_t launch_migrate(MigrateArgs a, int max_quant, int max_promote, bool beside, hipStream_t st);
 hipError_t launch_pack_tokens(const PackArgs& a, hipStream_t st);
 hipError_t launch_key_norm_init(const KeyNormArgs& a, hipStream_t st);
 hipError_t launch_score_pow(const ScorePowArgs& a, hipStream_t st);
@@ -428,7 +428,7 @@ hipError_t flush_routing(qevict_cache* c) {
     mp = std::max(mp, r.max_promote);
   }
   if (e == hipSuccess) e = timed(c, 2, rs, [&] { return launch_retier(ra, rs); }, n);
-  if (e == hipSuccess) e = timed(c, 3, rs, [&] { return launch_migrate(ma, mq, mp, rs); }, n);
+  if (e == hipSuccess) e = timed(c, 3, rs, [&] { return launch_migrate(ma, mq, mp, !c->queue_wait, rs); }, n);
   const int slot = c->next_batch_ev;
   c->next_batch_ev = (slot + 1) % (int)c->batch_ev.size();
   if (e == hipSuccess) e = hipEventRecord(c->batch_ev[slot], rs);
@@ -769,7 +769,7 @@ qevict_status qevict_prefill_assign(qevict_cache* c, int32_t layer, const uint16
   plan_next(g, c->cfg.max_context, prompt_len + 1, c->cfg.retier_interval, n_hist, &ra.unit[0]);
   if (e == hipSuccess) e = timed(c, 2, c->stream, [&] { return launch_retier(ra, c->stream); });
   MigrateArgs ma{gg, L, 1, {base}, k, v, prompt_len};
-  if (e == hipSuccess) e = timed(c, 3, c->stream, [&] { return launch_migrate(ma, g.K_q, g.K_f, c->stream); });
+  if (e == hipSuccess) e = timed(c, 3, c->stream, [&] { return launch_migrate(ma, g.K_q, g.K_f, false, c->stream); });
   if (e != hipSuccess) return hip_fail(e, "prefill launch");
   ls.T = prompt_len;
   ls.routed_end = n_hist;
@@ -984,7 +984,7 @@ qevict_status qevict_retier(qevict_cache* c, int32_t layer, qevict_retier_stats*
     RetierArgs ra{gg, L, 0, nullptr, 0, 1, {unit}};
     MigrateArgs ma{gg, L, 1, {base}, nullptr, nullptr, 0};
     e = timed(c, 2, c->stream, [&] { return launch_retier(ra, c->stream); });
-    if (e == hipSuccess) e = timed(c, 3, c->stream, [&] { return launch_migrate(ma, max_q, max_q, c->stream); });
+    if (e == hipSuccess) e = timed(c, 3, c->stream, [&] { return launch_migrate(ma, max_q, max_q, false, c->stream); });
   }
   if (e != hipSuccess) return hip_fail(e, "retier launch");
   if (a1 > a0) ls.routed_end = a1;
@@ -1061,7 +1061,7 @@ static qevict_status manual_move(qevict_cache* c, int layer, int seq, int window
   one.B = 1;
   MigrateArgs ma{one, L, 1, {unit_base(c, layer, seq)}, nullptr, nullptr, 0};
   e = launch_manual_move(ra, seq, window, to_quant, c->stream);
-  if (e == hipSuccess) e = launch_migrate(ma, 1, 1, c->stream);
+  if (e == hipSuccess) e = launch_migrate(ma, 1, 1, false, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(e, "manual move");
   return device_errors(c, layer);
