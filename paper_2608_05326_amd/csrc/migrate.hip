@@ -1075,16 +1075,19 @@ __global__ __launch_bounds__(256) void k_pack_tokens(PackArgs a) {
 }
 
 // The form with half a part per wave: two workgroups per (window, KV head) of the event's
-// windows or of eight, which most events after a single step stay below (with four, the
-// mean event below took 7.0 instead of 5.5 us), as long as that is a wave of workgroups
-// on the chip (six a compute unit) and some.  Larger launches are mostly idle workgroups,
-// whose number then counts, and take the form with fewer.  So does a batch that runs
-// beside attention, which its work delays and its latency does not, except with RoPE
-// (32K int4, eight layers, tiers turning over after every step: 21.5 us a step against
-// 22.4 with half a part per wave; with RoPE, under the queue-level wait, 43.6 and 31.6.
-// On one stream 68.5 and 42.4, RoPE 153 and 57.5).
+// windows or of a sixteenth of the kept ones, at most eight, which most events after a
+// single step stay below (511 windows kept: with four the mean event took 7.0 instead of
+// 5.5 us; 40 kept: eight cost 0.04 us an event in idle workgroups).  For launches of a
+// wave of workgroups on the chip (six a compute unit) and some; larger ones are mostly
+// idle workgroups, whose number then counts, and take the form with fewer.  So does a
+// batch that runs beside attention, which its work delays and its latency does not,
+// except with RoPE (32K int4, eight layers, tiers turning over after every step: 21.5 us a
+// step against 22.4 with half a part per wave; with RoPE, under the queue-level wait, 43.6
+// and 31.6.  On one stream 68.5 and 42.4, with RoPE 153 and 57.5).
 constexpr int kFewBlocks = 2048, kFewWindows = 8;
-static int few_blocks(const Geometry& g, int entries) { return 2 * g.H_kv * std::max(entries, kFewWindows); }
+static int few_blocks(const Geometry& g, int entries) {
+  return 2 * g.H_kv * std::max({entries, std::min(g.max_fq / 16, kFewWindows), 1});
+}
 
 // Workgroups for `entries` windows: one per (window, KV head), at most 16384
 // (larger events loop).  A prompt's migrations (2456 quantizations and 1632
