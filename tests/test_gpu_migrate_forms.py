@@ -30,8 +30,8 @@ def test_both_forms_match_oracle(W, bits, rope, R):
 @pytest.mark.parametrize("rope,most", [(0.0, 0.9), (5e5, 1.2)])
 def test_small_events_take_no_longer_than_the_rerank(rope, most):
     """A routing event after one decode step moves a few windows (4 here); their migrations run
-    side by side and take no longer than the re-rank before them (0.79 and 0.96 of its time
-    between events around the launches; 1.01 and 1.88 with a wave per part)."""
+    side by side and take no longer than the re-rank before them (0.81 and 1.0 of its time
+    between events around the launches; 0.97 and 1.66 with a wave per part)."""
     import torch
     import paper_2608_05326_amd as qv
     from tests.gpu_harness import gpu_config, to_dev_bf16
@@ -51,7 +51,7 @@ def test_small_events_take_no_longer_than_the_rerank(rope, most):
             moved += st["promotions"] + st["first_quantizations"]
             torch.cuda.synchronize()
             at.append([c.profile_read(i) for i in (2, 3)])
-        us = [1e3 * (at[-1][i][0] - at[9][i][0]) / (at[-1][i][1] - at[9][i][1]) for i in (0, 1)]
+        us = [1e3 * sorted(b[i][0] - a[i][0] for a, b in zip(at[9:], at[10:]))[25] for i in (0, 1)]   # medians
         print(f"re-rank {us[0]:.2f} us, migrations {us[1]:.2f} us an event of {moved / wl.steps:.1f} moves", flush=True)
         assert us[1] <= most * us[0], us
     finally:
