@@ -1544,18 +1544,35 @@ __global__ __launch_bounds__(kAttnThreads, MINB) void k_attend(AttnArgs a) {
 // guarded statistics loads a thread, of which four or eight were used, were 600
 // instructions, and at 1200 mass blocks bound the kernel): 4.5 -> 4.0 us at 32 heads
 // x 64 splits (8B, 32K), 8.8 -> 7.5 us at 4 x 64 heads x 16 splits (70B, 64K),
-// 4.3 -> 3.4 us at 8 heads (2K).
+// 4.3 -> 3.4 us at 8 heads (2K).  A second round, dependent on the first by its running
+// maximum, costs its latency and other bits: attention and merge of 64 heads x 64 splits
+// 21.9 us with two rounds of eight statistics, 21.3 with one of 16; 32 heads x 128 splits
+// with the rows past 64 read one by one 25.9, all at once 24.3.
 constexpr int kMergeThreads = 256;
 constexpr int kSplitGroups = 8;                     // split rows handled in parallel per output block
 
-// NSPT: split rows one output-block thread reads in its first round (further
-// splits, only with an explicit split count above 64, are read one by one)
 // Score update of the merge: attention masses (cumulative or decayed), the
 // attention p-norm, or key norms (separate instantiations, so the default one
 // carries no code of the others)
 enum MergeScore { kScoreMass = 0, kScorePNorm = 1, kScoreKeyNorm = 2 };
 
-template <int NSPT, int MS>
+// Mass blocks: consecutive threads that fold one head's split statistics.
+__host__ __device__ inline int merge_lanes(int heads) {
+  int P = 1;
+  while (2 * P * heads <= kMergeThreads && P < 64) P *= 2;
+  return P;
+}
+
+// Keeps a loaded value's load where it stands: from a select the compiler makes a guarded
+// load, and it moves loads behind a branch that decides whether they are used.
+__device__ __forceinline__ void pin(float2& v) { asm("" : "+v"(v.x), "+v"(v.y)); }
+__device__ __forceinline__ void pin(float4& v) { asm("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+
+// NSPT: split rows an output-block thread holds (>= S / 8); CR: split statistics a
+// mass-block thread holds (>= S / merge_lanes).  Read in one round, in blocks of at most
+// eight of which those past the last split are skipped (a scalar branch), and summed in
+// order relative to the maximum of all.
+template <int NSPT, int CR, int MS>
 __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
   const Geometry& G = a.g;
   const int blk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
@@ -1575,28 +1592,39 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
     // ---- output of head h: thread (c4, grp) owns channels 4c4..4c4+3 of splits grp + 8i ----
     const int h = blk;
     const int c4 = tid & 31, grp = tid >> 5;
-    // rounds of NSPT rows a thread (one round with at most 8 NSPT splits); a row past
-    // the last split reads that one again and becomes zeros (its weight is 0, but 0
-    // times an infinite partial would be NaN)
-    auto stat = [&](int sp) {
-      float2 v = pml[(int64_t)h * S + min(sp, S - 1)];
-      v.x = sp < S ? v.x : -INFINITY;
-      return v;
-    };
+    // a row past the last split reads that one again and becomes zeros (its weight is 0,
+    // but 0 times an infinite partial would be NaN)
+    constexpr int BLK = NSPT < 8 ? NSPT : 8;
     float4 o[NSPT];
     float2 ml[NSPT];
-#pragma unroll
-    for (int i = 0; i < NSPT; ++i) {
-      const int sp = grp + kSplitGroups * i;
-      const float4 x = *(const float4*)(part + ((int64_t)h * S + min(sp, S - 1)) * kHeadDim + 4 * c4);
-      const bool ok = sp < S;
-      o[i] = make_float4(ok ? x.x : 0.f, ok ? x.y : 0.f, ok ? x.z : 0.f, ok ? x.w : 0.f);
-      ml[i] = stat(sp);
-    }
     float m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < NSPT; ++i) m = fmaxf(m, ml[i].x);
-    for (int sp = grp + kSplitGroups * NSPT; sp < S; sp += kSplitGroups) m = fmaxf(m, stat(sp).x);
+    for (int i0 = 0; i0 < NSPT; i0 += BLK) {
+      if (i0 == 0 || kSplitGroups * i0 < S) {   // uniform
+#pragma unroll
+        for (int i = i0; i < i0 + BLK; ++i) {
+          const int sp = grp + kSplitGroups * i, row = min(sp, S - 1);
+          o[i] = *(const float4*)(part + ((int64_t)h * S + row) * kHeadDim + 4 * c4);
+          ml[i] = pml[(int64_t)h * S + row];
+        }
+      } else {
+#pragma unroll
+        for (int i = i0; i < i0 + BLK; ++i) {
+          o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+          ml[i] = make_float2(-INFINITY, 0.f);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // all loads first
+#pragma unroll
+    for (int i = 0; i < NSPT; ++i) {
+      const bool ok = grp + kSplitGroups * i < S;
+      pin(ml[i]);
+      pin(o[i]);
+      o[i] = make_float4(ok ? o[i].x : 0.f, ok ? o[i].y : 0.f, ok ? o[i].z : 0.f, ok ? o[i].w : 0.f);
+      ml[i].x = ok ? ml[i].x : -INFINITY;
+      m = fmaxf(m, ml[i].x);
+    }
     if (c4 == 0) sml[0][grp] = m;
     __syncthreads();
     float M = -INFINITY;
@@ -1604,19 +1632,16 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
     for (int q = 0; q < kSplitGroups; ++q) M = fmaxf(M, sml[0][q]);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float lsum = 0.f;
-    auto add = [&](float4 x, float2 st) {
-      const float f = __builtin_amdgcn_exp2f(st.x - M);   // 0 for a split without items
-      acc.x += f * x.x;
-      acc.y += f * x.y;
-      acc.z += f * x.z;
-      acc.w += f * x.w;
-      lsum += f * st.y;
-    };
     if (M > -INFINITY) {
 #pragma unroll
-      for (int i = 0; i < NSPT; ++i) add(o[i], ml[i]);
-      for (int sp = grp + kSplitGroups * NSPT; sp < S; sp += kSplitGroups)
-        add(*(const float4*)(part + ((int64_t)h * S + sp) * kHeadDim + 4 * c4), stat(sp));
+      for (int i = 0; i < NSPT; ++i) {
+        const float f = __builtin_amdgcn_exp2f(ml[i].x - M);   // 0 for a split without items
+        acc.x += f * o[i].x;
+        acc.y += f * o[i].y;
+        acc.z += f * o[i].z;
+        acc.w += f * o[i].w;
+        lsum += f * ml[i].y;
+      }
     }
     sred[grp][c4] = acc;
     if (c4 == 0) sml[1][grp] = lsum;
@@ -1661,36 +1686,36 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(AttnArgs a) {
   const float2 mr = mref[(int64_t)cpos * nh + hh];
   const int wl = iwin[min(pos, G.max_fq)];   // used when pos < n_fq
   const float old_score = iscore[cpos];
-  // M_h, L_h: P consecutive threads per head (P a power of two, P * H_q <= 256,
+  // M_h, L_h: P consecutive threads per head (P a power of two, P * H_q <= 256, 4 <=
   // P <= 64 so that the P threads of a head sit in one wave), thread j folds
   // splits j, j + P, j + 2P, ... (consecutive threads read consecutive rows),
   // then a butterfly over the P lanes combines the (max, sum) pairs
-  int P = 1;
-  while (2 * P * nh <= kMergeThreads && P < 64) P *= 2;
-  // splits in rounds of kRound rows a thread (one round with the automatic split
-  // counts); each round's loads are issued together
-  constexpr int kRound = 8;
+  const int P = merge_lanes(nh);
   {
     const int h = min(tid / P, nh - 1), j = tid % P;
     const bool hv = tid / P < nh;
     const float2* row = pml + (int64_t)h * S;
+    float2 st[CR];
+#pragma unroll
+    for (int i0 = 0; i0 < CR; i0 += 8) {
+      if (i0 == 0 || P * i0 < S) {   // uniform
+#pragma unroll
+        for (int i = i0; i < i0 + 8; ++i) st[i] = row[min(j + P * i, S - 1)];
+      } else {
+#pragma unroll
+        for (int i = i0; i < i0 + 8; ++i) st[i] = make_float2(-INFINITY, 0.f);
+      }
+    }
     float m = -INFINITY, l = 0.f;
-    for (int sp0 = j; sp0 - j < S; sp0 += kRound * P) {
-      float2 st[kRound];
 #pragma unroll
-      for (int i = 0; i < kRound; ++i) st[i] = row[min(sp0 + P * i, S - 1)];
-      float mn = m;
+    for (int i = 0; i < CR; ++i) {
+      pin(st[i]);
+      st[i].x = j + P * i < S ? st[i].x : -INFINITY;
+      m = fmaxf(m, st[i].x);
+    }
+    if (m > -INFINITY) {
 #pragma unroll
-      for (int i = 0; i < kRound; ++i) {
-        st[i].x = sp0 + P * i < S ? st[i].x : -INFINITY;
-        mn = fmaxf(mn, st[i].x);
-      }
-      if (mn > -INFINITY) {
-        l = m > -INFINITY ? l * __builtin_amdgcn_exp2f(m - mn) : 0.f;
-#pragma unroll
-        for (int i = 0; i < kRound; ++i) l += st[i].y * __builtin_amdgcn_exp2f(st[i].x - mn);   // exp2(-inf) = 0
-        m = mn;
-      }
+      for (int i = 0; i < CR; ++i) l += st[i].y * __builtin_amdgcn_exp2f(st[i].x - m);   // exp2(-inf) = 0
     }
     for (int o = 1; o < P; o <<= 1) {
       const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64);
@@ -1840,12 +1865,17 @@ hipError_t launch_merge(const AttnArgs& a, hipStream_t st) {
   const int per_blk = kMergeThreads / a.g.H_q;
   const int n_mass = (a.g.max_items + per_blk - 1) / per_blk;
   dim3 grid(a.g.H_q + n_mass, a.g.B);
-  const int need = (a.g.n_split + kSplitGroups - 1) / kSplitGroups;
+  // rows an output-block thread and statistics a mass-block thread hold (at most 32 each:
+  // 256 splits, splits x heads 4096, heads 64)
+  const int rows = (a.g.n_split + kSplitGroups - 1) / kSplitGroups;
+  const int P = merge_lanes(a.g.H_q), stats = (a.g.n_split + P - 1) / P;
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(kMergeThreads), 0, st, a); };
   auto by_split = [&](auto ms) {
     constexpr int MS = decltype(ms)::value;
-    if (need <= 4) go(k_merge<4, MS>);
-    else go(k_merge<8, MS>);
+    if (rows <= 4) go(k_merge<4, 8, MS>);             // (at most 32 splits over at least 4 lanes)
+    else if (rows <= 8 && stats <= 8) go(k_merge<8, 8, MS>);
+    else if (rows <= 8) go(k_merge<8, 16, MS>);       // more than 32 heads, 33 to 64 splits
+    else go(k_merge<32, 32, MS>);                     // an explicit split count above 64
   };
   if (a.key_norm) by_split(std::integral_constant<int, kScoreKeyNorm>{});
   else if (a.pnorm_p > 0.f) by_split(std::integral_constant<int, kScorePNorm>{});

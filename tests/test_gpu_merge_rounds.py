@@ -1,5 +1,5 @@
-"""Split merge where a thread reads its split rows in several rounds: just past one
-round, a partial second one and the largest split count, against the oracle."""
+"""Split merge where a thread holds more than eight split rows or statistics: just past
+eight, partial blocks of eight and the largest split counts, against the oracle."""
 import pytest
 
 import synthetic as syn
@@ -7,7 +7,8 @@ import synthetic as syn
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("name,splits", [("c2s", 33), ("c2s", 65), ("c2s", 127), ("c6w8s", 128)])
+@pytest.mark.parametrize("name,splits", [("c2s", 33), ("c2s", 65), ("c2s", 127), ("c6w8s", 128),
+                                         ("c5s", 33), ("c5s", 63), ("c5s", 64)])   # 64 heads
 def test_merge_of_many_splits(name, splits):
     from tests.gpu_harness import Lockstep
     ls = Lockstep(syn.get_workload(name), num_splits=splits, steps=10)
